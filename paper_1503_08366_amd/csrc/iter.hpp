@@ -140,13 +140,13 @@ __device__ __forceinline__ void control_preview_body(const IterArgs<T> &p, int p
 template <typename T> struct HalfStep {
   T h, dual, proj_in, vt;
 };
-template <typename T>
+template <typename T, bool GROUPED = false>
 __device__ __forceinline__ HalfStep<T> half_step(int fh, T fa, T fb, T fc, T fd, T fe, T v, T vt, T rho, T resc,
                                                  T alpha) {
   HalfStep<T> r;
   if (resc != T(1)) vt *= resc;
   const T arg = v - vt;
-  r.h = prox_param<T>(fh, fa, fb, fc, fd, fe, arg, rho);
+  r.h = prox_param<T, GROUPED>(fh, fa, fb, fc, fd, fe, arg, rho);
   r.dual = -rho * (r.h - arg);
   const T rel = alpha * r.h + (T(1) - alpha) * v;
   r.proj_in = rel + vt;
@@ -159,8 +159,8 @@ __device__ __forceinline__ HalfStep<T> half_step(int fh, T fa, T fb, T fc, T fd,
 // ---------------------------------------------------------------------------
 // With CG (the CGLS projection) the state is read as that projection leaves
 // it: x~ = c - x, y = d - r1, y~ = r1 (r1 kept in yt), and x is set to the
-// half step x_h, where the next projection starts.
-template <typename T, bool CG = false>
+// half step x_h, where the next projection starts.  GROUPED: see prox_logistic.
+template <typename T, bool CG = false, bool GROUPED = false>
 __device__ __forceinline__ void prox_body(const Blk &b, const IterArgs<T> &p) {
   __shared__ double bs[4 * (kBlock / kWave)];
   __shared__ CtrlState st;
@@ -212,7 +212,7 @@ __device__ __forceinline__ void prox_body(const Blk &b, const IterArgs<T> &p) {
   const bool gap = !CG && p.ctrl->stop_gap;
   double contrib = 0.0, gobj = 0.0, gconj = 0.0;
   if (i < len) {
-    const HalfStep<T> hs = half_step<T>(fh, fa, fb, fc, fd, fe, vi, vti, rho, resc, alpha);
+    const HalfStep<T> hs = half_step<T, GROUPED>(fh, fa, fb, fc, fd, fe, vi, vti, rho, resc, alpha);
     if constexpr (!CG) {
       if (resc != T(1)) vt[i] = hs.vt;
     }
