@@ -308,7 +308,8 @@ int pogs_prox_noalloc(const pogs_fn *fn, pogs_dtype dt, double rho, const void *
  * on the context (its functions and iterate are reused).  With the stop test
  * disabled it runs `reps` full iterations as captured launch sequences, then
  * `reps` back-to-back launches of each iteration kernel alone, and writes
- *   ms[0] average ms per full iteration,
+ *   ms[0] average ms per full iteration (in the launches a residual-rule solve
+ *   on the context uses),
  *   direct projection: ms[1] prox step, ms[2] first pass over A, ms[3] solve
  *   with the cached inverse, ms[4] second pass over A; when m >= n the prox
  *   step runs inside the first pass and its finish (ms[1] = 0, ms[2] covers

@@ -138,7 +138,7 @@ void fill_result(const GStatus &st, pogs_result *out, double ms_solve) {
 // Whole-GPU path for one problem (used for problems too large for a workgroup).
 int solve_large(const HostProblem &hp, pogs_result *out, hipStream_t s) {
   pogs_ctx *ctx = nullptr;
-  int rc = pogs_init(&ctx, hp.m, hp.n, hp.A.get(), POGS_F32, POGS_ROW_MAJOR, hp.n, POGS_HOST, &hp.params, s);
+  int rc = init_context(&ctx, hp.m, hp.n, hp.A.get(), POGS_F32, POGS_ROW_MAJOR, hp.n, POGS_HOST, &hp.params, s, false);
   if (rc) return rc;
   std::vector<uint8_t> fh(hp.f.h), gh(hp.g.h);
   pogs_fn f{hp.m, 1, fh.data(), hp.f.a.data(), hp.f.b.data(), hp.f.c.data(), hp.f.d.data(), hp.f.e.data()};

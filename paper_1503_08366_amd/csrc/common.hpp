@@ -94,6 +94,16 @@ __device__ inline double wave_sum_dpp(double v) {
   return swap_pair_sum32(v);
 }
 
+// Sum over each row of 16 lanes, and over each half of 32, by the first steps
+// of wave_sum_dpp (every lane of the group receives the total).
+__device__ inline double row16_sum_dpp(double v) {
+  v = dpp_pair_sum(v, 0xB1);
+  v = dpp_pair_sum(v, 0x4E);
+  v = dpp_pair_sum(v, 0x141);
+  return dpp_pair_sum(v, 0x140);
+}
+__device__ inline double half32_sum_dpp(double v) { return swap_pair_sum16(row16_sum_dpp(v)); }
+
 // Sum over groups of W consecutive lanes (W a power of two <= 64).
 template <int W> __device__ inline double group_sum(double v) {
 #pragma unroll

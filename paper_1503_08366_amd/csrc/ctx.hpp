@@ -282,6 +282,12 @@ struct pogs_ctx {
   int graph_gap = 0;     // the captured graph runs the gap test
   int nt_rows = 0, nt_cols = 0;  // load policy of the passes over A (size rule or autotuned)
   bool solved = false;  // functions uploaded by a previous solve
+  // resident solve: its shape, exchange buffers, the transposed matrix (m < n),
+  // the number after the last exchange
+  ResGeom res;
+  void *res_x = nullptr, *At = nullptr;
+  unsigned res_epoch = 0;
+  bool res_wanted = true;  // false: the contexts of the batch call and the serving engine (see init_context)
 
   size_t esz() const { return dt == POGS_F32 ? 4 : 8; }
   template <typename T> T *vecp(int idx) const {
@@ -372,6 +378,8 @@ struct pogs_ctx {
     }
     return p;
   }
+  // The long-side-as-rows matrix of the resident solve.
+  template <typename T> const T *res_matrix() const { return (const T *)(m < n ? At : A); }
   ~pogs_ctx() {
     if (graph) (void)hipGraphExecDestroy(graph);
     // device memory goes back to the pool in the order of the context's
@@ -389,3 +397,9 @@ struct pogs_ctx {
   }
 };
 
+// pogs_init; resident = false leaves the resident solve out: the batch call's
+// and the serving engine's contexts share the GPU with grouped rounds and with
+// each other, so they keep to launches that need no CU to themselves (and
+// to the memory the engine charges for them).
+int init_context(pogs_ctx **out, int64_t m, int64_t n, const void *A, pogs_dtype dt, pogs_order ord, int64_t lda,
+                 pogs_mem mem, const pogs_params *params, void *stream, bool resident);

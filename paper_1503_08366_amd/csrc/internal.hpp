@@ -54,6 +54,8 @@ struct Ctrl {
   CgState cg;
   double spec_rho[2];  // one-pass iteration: the rho with which the previous iteration's
                        // one-pass kernel formed the half step of parity i's iteration
+  unsigned res_e1, res_e2;  // resident solve: numbers of the last exchanges
+  int res_failed;           // resident solve: a workgroup gave up waiting
 };
 
 // Separable function as device arrays (per element).
@@ -265,6 +267,25 @@ template <typename T> void launch_iteration_cg_sparse_part(const IterArgs<T> &p,
 template <typename T>
 void launch_warm_start_sparse(const IterArgs<T> &p, const double *D, const double *E, double rho0, const T *x0,
                               const T *nu0, hipStream_t s);
+
+// Resident solve (resident.hip): G workgroups (0: the shape is not taken), the
+// kernel (pieces per lane and row, rows per wave) and nc columns of the short
+// side per workgroup.
+struct ResGeom {
+  int G = 0, pieces = 0, rpw = 0, nc = 0;
+};
+// Workgroups of resident solves that fit the device together (its CUs).
+int res_capacity();
+ResGeom res_geometry(int64_t m, int64_t n, int elem_size);
+// Bytes of the exchange buffers (zero them before the first launch).
+size_t res_exchange_bytes(const ResGeom &r, int elem_size);
+struct ResHost;
+// One launch of `iters` iterations; first: of a solve.
+template <typename T>
+int launch_resident(const IterArgs<T> &p, const ResGeom &r, const T *M, void *xbuf, ResHost *host, int first, int iters,
+                    hipStream_t s);
+// Transpose of the scaled matrix (m x n, row stride ld) into n x m rows of stride ldt, padding zeroed.
+template <typename T> void launch_transpose(const T *A, int m, int n, int ld, T *At, int ldt, hipStream_t s);
 
 // Iteration geometry helpers.
 int gemv_t_tile(int elem_size);

@@ -71,48 +71,52 @@ __device__ inline void block_sum4(double v[4], double *scratch /* 4 * waves */) 
     }
 }
 
+// The stopping test (Section 3.4) and Algorithm 3 for iteration st.k with the
+// given residuals and tolerances; updates st.
+__device__ inline void control_decide(const Ctrl &q, CtrlState &st, double r_pri, double eps_pri, double r_dual,
+                                      double eps_dual) {
+  st.r_pri = r_pri;
+  st.r_dual = r_dual;
+  st.eps_pri = eps_pri;
+  st.eps_dual = eps_dual;
+  const int k = st.k;
+  double rescale = 1.0;
+  int done = 0;
+  if (!isfinite(r_pri) || !isfinite(r_dual)) {
+    done = 1 + POGS_NUMERICAL;
+  } else if (!q.stop_gap && r_pri < eps_pri && r_dual < eps_dual) {
+    done = 1 + POGS_CONVERGED;
+  } else {
+    if (q.adaptive) {
+      const double rho = st.rho;
+      double rho_new = rho;
+      if (r_dual < eps_dual && q.tau * k > st.l) {
+        rho_new = q.delta * rho;
+        st.u = k;
+      } else if (r_pri < eps_pri && q.tau * k > st.u) {
+        rho_new = rho / q.delta;
+        st.l = k;
+      }
+      if (rho_new != rho) {
+        rescale = rho / rho_new;
+        st.rho = rho_new;
+      }
+    }
+    if (k + 1 >= q.max_iter) done = 1 + POGS_MAXITER;
+  }
+  st.rescale = rescale;
+  st.k = k + 1;
+  st.done = done;
+  st.pending = 0;
+}
+
 template <typename T>
 __device__ void control_apply(const IterArgs<T> &p, double part[4], CtrlState &st, double *lds) {
   block_sum4(part, lds);
   if (threadIdx.x == 0) {
     const Ctrl &q = *p.ctrl;
-    const double mu2 = part[0], yh2 = part[1], pri2 = part[2], dual2 = part[3];
-    const double r_pri = sqrt(pri2), r_dual = sqrt(dual2);
-    const double eps_pri = q.eps_abs + q.eps_rel * sqrt(yh2);
-    const double eps_dual = q.eps_abs + q.eps_rel * sqrt(mu2);
-    st.r_pri = r_pri;
-    st.r_dual = r_dual;
-    st.eps_pri = eps_pri;
-    st.eps_dual = eps_dual;
-    const int k = st.k;
-    double rescale = 1.0;
-    int done = 0;
-    if (!isfinite(r_pri) || !isfinite(r_dual)) {
-      done = 1 + POGS_NUMERICAL;
-    } else if (!q.stop_gap && r_pri < eps_pri && r_dual < eps_dual) {
-      done = 1 + POGS_CONVERGED;
-    } else {
-      if (q.adaptive) {
-        const double rho = st.rho;
-        double rho_new = rho;
-        if (r_dual < eps_dual && q.tau * k > st.l) {
-          rho_new = q.delta * rho;
-          st.u = k;
-        } else if (r_pri < eps_pri && q.tau * k > st.u) {
-          rho_new = rho / q.delta;
-          st.l = k;
-        }
-        if (rho_new != rho) {
-          rescale = rho / rho_new;
-          st.rho = rho_new;
-        }
-      }
-      if (k + 1 >= q.max_iter) done = 1 + POGS_MAXITER;
-    }
-    st.rescale = rescale;
-    st.k = k + 1;
-    st.done = done;
-    st.pending = 0;
+    control_decide(q, st, sqrt(part[2]), q.eps_abs + q.eps_rel * sqrt(part[1]), sqrt(part[3]),
+                   q.eps_abs + q.eps_rel * sqrt(part[0]));
   }
   __syncthreads();
 }

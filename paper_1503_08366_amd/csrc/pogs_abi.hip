@@ -5,8 +5,10 @@
 #include <cfloat>
 #include <cmath>
 #include <chrono>
+#include <condition_variable>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -15,6 +17,7 @@
 #include "prox.hpp"
 #include "hostutil.hpp"
 #include "ctx.hpp"
+#include "resident.hpp"
 #include "upload.hpp"
 
 using namespace pogs;
@@ -157,6 +160,16 @@ template <typename T> int init_impl(pogs_ctx *c, const void *A, pogs_dtype sdt, 
     if ((rc = tmp.alloc(&ws, std::max(gb, fb)))) return rc;
     if ((rc = run_gram<T>((const T *)c->A, m, n, c->ld, K, Q, (float *)ws, (double *)ws, gb, s))) return rc;
     if ((rc = run_factor_inverse<T>(K, c->q, Q, (T *)c->Kinv, c->ldk, (double *)ws, flags + 1, s))) return rc;
+  }
+  if (c->res_wanted) c->res = res_geometry(m, n, sizeof(T));
+  if (c->res.G) {
+    const size_t xb = res_exchange_bytes(c->res, sizeof(T));
+    if (c->arena.alloc(&c->res_x, xb) || (m < n && c->arena.alloc(&c->At, (size_t)n * c->ldk * sizeof(T)))) {
+      c->res = ResGeom{};  // no memory for it: one launch per step
+    } else {
+      POGS_HIP_TRY(hipMemsetAsync(c->res_x, 0, xb, s));
+      if (m < n) launch_transpose<T>((const T *)c->A, m, n, c->ld, (T *)c->At, c->ldk, s);
+    }
   }
   // read back once pogs_init has queued the rest of its work (the frees of
   // the temporaries above go in stream order meanwhile)
@@ -311,6 +324,11 @@ template <typename T> int tune_loads(pogs_ctx *c) {
 
 extern "C" int pogs_init(pogs_ctx **out, int64_t m, int64_t n, const void *A, pogs_dtype dt, pogs_order ord,
                          int64_t lda, pogs_mem mem, const pogs_params *params, void *stream) {
+  return init_context(out, m, n, A, dt, ord, lda, mem, params, stream, true);
+}
+
+int init_context(pogs_ctx **out, int64_t m, int64_t n, const void *A, pogs_dtype dt, pogs_order ord, int64_t lda,
+                 pogs_mem mem, const pogs_params *params, void *stream, bool resident) {
   if (!out) return POGS_EINVAL;
   *out = nullptr;
   if (m <= 0 || n <= 0 || !A || m > (1LL << 31) - 1 || n > (1LL << 31) - 1) return POGS_EINVAL;
@@ -333,6 +351,7 @@ extern "C" int pogs_init(pogs_ctx **out, int64_t m, int64_t n, const void *A, po
   c->dt = dt;
   c->params = p;
   c->proj = p.projection;
+  c->res_wanted = resident;
   c->ld = (int)round_up(n, 64);
   c->q = (int)std::min(m, n);
   c->Q = (int)round_up(c->q, 64);
@@ -625,55 +644,10 @@ template <typename T> int ensure_graph(pogs_ctx *c, int chunk, int cg_cap, int g
   return POGS_OK;
 }
 
-template <typename T> int solve_impl(pogs_ctx *c, const pogs_fn *f, const pogs_fn *g, const pogs_params &p,
-                                     const void *x0, const void *nu0, pogs_result *out) {
-  const double t0 = now_ms();
-  const int m = (int)c->m, n = (int)c->n;
+// The iterations of a solve with one launch per step, in chunks.
+template <typename T> int run_chunks(pogs_ctx *c, const pogs_params &p, int chunk, int cg_cap, int gap) {
   hipStream_t s = c->stream;
-  const int cg_cap = p.projection == POGS_PROJ_CGLS ? p.cg_max_iter : 0;
-  const int gap = p.stop_rule == POGS_STOP_GAP ? 1 : 0;
   int rc;
-  if ((rc = upload_fns<T>(c, f, g))) return rc;  // validates f and g first
-  // tall float32 direct solves with the residual rule read A once per iteration
-  c->fused = c->fp_blocks > 0 && cg_cap == 0 && !gap;
-  // zero state (Algorithm 1 starts from x = y = x~ = y~ = 0), or the warm start
-  POGS_HIP_TRY(hipMemsetAsync(c->vec, 0, c->vec_elems() * sizeof(T), s));
-  if (x0 || nu0) {
-    const T *dx0 = (const T *)x0, *dnu0 = (const T *)nu0;
-    if (out->mem == POGS_HOST) {  // staged in the output vectors (written again at the end)
-      if (x0) {
-        POGS_HIP_TRY(hipMemcpyAsync(c->vecp<T>(11), x0, (size_t)n * sizeof(T), hipMemcpyHostToDevice, s));
-        dx0 = c->vecp<T>(11);
-      }
-      if (nu0) {
-        POGS_HIP_TRY(hipMemcpyAsync(c->vecp<T>(14), nu0, (size_t)m * sizeof(T), hipMemcpyHostToDevice, s));
-        dnu0 = c->vecp<T>(14);
-      }
-    }
-    if (c->sparse) launch_warm_start_sparse<T>(c->iter_args<T>(), c->D, c->E, p.rho0, dx0, dnu0, s);
-    else launch_warm_start<T>(c->iter_args<T>(), c->splits, c->rps, c->ncolp, c->D, c->E, p.rho0, dx0, dnu0, s);
-    if (cg_cap > 0) launch_cg_from_state<T>(c->iter_args<T>(), s);
-    if (out->mem == POGS_HOST) POGS_HIP_TRY(hipStreamSynchronize(s));  // host x0, nu0 may be pageable
-  }
-  Ctrl h{};
-  h.eps_abs = p.eps_abs;
-  h.eps_rel = p.eps_rel;
-  h.alpha = p.alpha;
-  h.delta = p.delta;
-  h.tau = p.tau;
-  h.max_iter = p.max_iter;
-  h.adaptive = p.adaptive_rho ? 1 : 0;
-  for (int b = 0; b < 2; ++b) {  // iteration 0 reads st[1]: no stop test pending
-    h.st[b].rho = p.rho0;
-    h.st[b].rescale = 1.0;
-  }
-  h.cg_tol = p.cg_tol;
-  h.cg_cap = cg_cap;
-  h.stop_gap = gap;
-  h.cg.stop = -1;
-  *c->ctrl_host = h;
-  POGS_HIP_TRY(hipMemcpyAsync(c->ctrl, c->ctrl_host, sizeof(Ctrl), hipMemcpyHostToDevice, s));
-  const int chunk = even_chunk(p.chunk_iters);
   // Large problems launch every chunk directly: an iteration keeps the GPU
   // busy longer than the host takes to issue it, and a graph would only add
   // its capture and, at pogs_free, its destruction (about 1 ms for a chunk of
@@ -713,6 +687,146 @@ template <typename T> int solve_impl(pogs_ctx *c, const pogs_fn *f, const pogs_f
               cs.eps_pri, cs.r_dual, cs.eps_dual, cs.rho);
     if (cs.done) break;
     if (direct) launch_iters<T>(c, kLookahead, chunk, true, cg_cap, gap, s);
+  }
+  return POGS_OK;
+}
+
+// Workgroups of resident solves on one GPU at once, over all threads: each
+// solve needs all of its workgroups on the GPU together, so the sum stays
+// within the CU count (one workgroup per CU always fits; other kernels end by
+// themselves).  First come, first served.
+class ResSlots {
+ public:
+  void acquire(int g) {
+    std::unique_lock<std::mutex> lk(mu_);
+    const unsigned long long mine = tail_++;
+    cv_.wait(lk, [&] { return mine == head_ && (used_ == 0 || used_ + g <= res_capacity()); });
+    used_ += g;
+    ++head_;
+    cv_.notify_all();
+  }
+  void release(int g) {
+    std::lock_guard<std::mutex> lk(mu_);
+    used_ -= g;
+    cv_.notify_all();
+  }
+  static ResSlots &of_device() {
+    static ResSlots s[64];
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    return s[dev & 63];
+  }
+
+ private:
+  std::mutex mu_;
+  std::condition_variable cv_;
+  int used_ = 0;
+  unsigned long long head_ = 0, tail_ = 0;
+};
+struct ResHold {
+  ResSlots &s;
+  int g;
+  explicit ResHold(int n) : s(ResSlots::of_device()), g(n) { s.acquire(g); }
+  ~ResHold() { s.release(g); }
+};
+
+// The iterations of a solve as resident launches of `chunk` iterations, each
+// queued while the host waits for the one before (after the launch that stops,
+// the next one returns at once).  *failed: a workgroup gave up waiting; the
+// state is then meaningless.
+template <typename T> int run_resident(pogs_ctx *c, int chunk, int verbose, bool *failed) {
+  hipStream_t s = c->stream;
+  hipEvent_t done = thread_event();
+  if (!done) return POGS_EDEVICE;
+  ResHost *h = (ResHost *)c->flags_host;
+  *h = ResHost{};
+  ResHold hold(c->res.G);
+  int rc;
+  const IterArgs<T> p = c->iter_args<T>();
+  auto launch = [&](int first) {
+    return launch_resident<T>(p, c->res, c->res_matrix<T>(), c->res_x, h, first, chunk, s);
+  };
+  if ((rc = launch(1))) return rc;
+  for (;;) {
+    POGS_HIP_TRY(hipEventRecord(done, s));
+    if ((rc = launch(0))) return rc;
+    POGS_HIP_TRY(hipEventSynchronize(done));
+    const CtrlState cs = h->st;
+    if (verbose)
+      fprintf(stderr, "pogs: k=%d r_pri=%.3e eps_pri=%.3e r_dual=%.3e eps_dual=%.3e rho=%.4g\n", cs.k, cs.r_pri,
+              cs.eps_pri, cs.r_dual, cs.eps_dual, cs.rho);
+    *failed = *(volatile int *)&h->failed != 0;
+    if (*failed || cs.done) break;
+  }
+  POGS_HIP_TRY(hipStreamSynchronize(s));
+  *failed = h->failed != 0;
+  c->ctrl_host->st[0] = h->st;
+  c->res_epoch = *failed ? c->res_epoch + (1u << 20) : std::max(h->e1, h->e2) + 2;
+  return POGS_OK;
+}
+
+template <typename T> int solve_impl(pogs_ctx *c, const pogs_fn *f, const pogs_fn *g, const pogs_params &p,
+                                     const void *x0, const void *nu0, pogs_result *out) {
+  const double t0 = now_ms();
+  const int m = (int)c->m, n = (int)c->n;
+  hipStream_t s = c->stream;
+  const int cg_cap = p.projection == POGS_PROJ_CGLS ? p.cg_max_iter : 0;
+  const int gap = p.stop_rule == POGS_STOP_GAP ? 1 : 0;
+  int rc;
+  if ((rc = upload_fns<T>(c, f, g))) return rc;  // validates f and g first
+  const int chunk = even_chunk(p.chunk_iters);
+  auto start = [&](bool fused) -> int {
+    c->fused = fused;
+    // zero state (Algorithm 1 starts from x = y = x~ = y~ = 0), or the warm start
+    POGS_HIP_TRY(hipMemsetAsync(c->vec, 0, c->vec_elems() * sizeof(T), s));
+    if (x0 || nu0) {
+      const T *dx0 = (const T *)x0, *dnu0 = (const T *)nu0;
+      if (out->mem == POGS_HOST) {  // staged in the output vectors (written again at the end)
+        if (x0) {
+          POGS_HIP_TRY(hipMemcpyAsync(c->vecp<T>(11), x0, (size_t)n * sizeof(T), hipMemcpyHostToDevice, s));
+          dx0 = c->vecp<T>(11);
+        }
+        if (nu0) {
+          POGS_HIP_TRY(hipMemcpyAsync(c->vecp<T>(14), nu0, (size_t)m * sizeof(T), hipMemcpyHostToDevice, s));
+          dnu0 = c->vecp<T>(14);
+        }
+      }
+      if (c->sparse) launch_warm_start_sparse<T>(c->iter_args<T>(), c->D, c->E, p.rho0, dx0, dnu0, s);
+      else launch_warm_start<T>(c->iter_args<T>(), c->splits, c->rps, c->ncolp, c->D, c->E, p.rho0, dx0, dnu0, s);
+      if (cg_cap > 0) launch_cg_from_state<T>(c->iter_args<T>(), s);
+      if (out->mem == POGS_HOST) POGS_HIP_TRY(hipStreamSynchronize(s));  // host x0, nu0 may be pageable
+    }
+    Ctrl h{};
+    h.eps_abs = p.eps_abs;
+    h.eps_rel = p.eps_rel;
+    h.alpha = p.alpha;
+    h.delta = p.delta;
+    h.tau = p.tau;
+    h.max_iter = p.max_iter;
+    h.adaptive = p.adaptive_rho ? 1 : 0;
+    for (int b = 0; b < 2; ++b) {  // iteration 0 reads st[1]: no stop test pending
+      h.st[b].rho = p.rho0;
+      h.st[b].rescale = 1.0;
+    }
+    h.cg_tol = p.cg_tol;
+    h.cg_cap = cg_cap;
+    h.stop_gap = gap;
+    h.cg.stop = -1;
+    h.res_e1 = h.res_e2 = c->res_epoch;
+    *c->ctrl_host = h;
+    POGS_HIP_TRY(hipMemcpyAsync(c->ctrl, c->ctrl_host, sizeof(Ctrl), hipMemcpyHostToDevice, s));
+    return POGS_OK;
+  };
+  bool stepwise = true;  // one launch per step of an iteration
+  if (c->res.G && cg_cap == 0 && !gap) {
+    bool failed = false;
+    if ((rc = start(false)) || (rc = run_resident<T>(c, chunk, p.verbose, &failed))) return rc;
+    stepwise = failed;
+    if (failed) c->res = ResGeom{};  // the GPU is shared in a way that keeps the workgroups apart
+  }
+  if (stepwise) {
+    // tall float32 direct solves with the residual rule read A once per iteration
+    if ((rc = start(c->fp_blocks > 0 && cg_cap == 0 && !gap)) || (rc = run_chunks<T>(c, p, chunk, cg_cap, gap))) return rc;
   }
   // unscale into the caller's buffers (device) or staging (host); the
   // one-pass iteration left the last iteration's half step in set (k - 1) % 2
@@ -777,6 +891,7 @@ template <typename T> int profile_impl(pogs_ctx *c, int reps, double *ms) {
   h.cg_tol = c->params.cg_tol;
   h.cg_cap = cg_cap;
   h.cg.stop = -1;
+  h.res_e1 = h.res_e2 = c->res_epoch;
   *c->ctrl_host = h;
   POGS_HIP_TRY(hipMemcpyAsync(c->ctrl, c->ctrl_host, sizeof(Ctrl), hipMemcpyHostToDevice, s));
   const int chunk = even_chunk(c->params.chunk_iters);
@@ -787,14 +902,26 @@ template <typename T> int profile_impl(pogs_ctx *c, int reps, double *ms) {
   POGS_HIP_TRY(hipEventCreate(&e1));
   float t = 0.f;
   const int launches = (int)cdiv(reps, chunk);
-  POGS_HIP_TRY(hipGraphLaunch(c->graph, s));  // warm
-  POGS_HIP_TRY(hipEventRecord(e0, s));
-  for (int i = 0; i < launches; ++i) POGS_HIP_TRY(hipGraphLaunch(c->graph, s));
-  POGS_HIP_TRY(hipEventRecord(e1, s));
-  POGS_HIP_TRY(hipEventSynchronize(e1));
-  POGS_HIP_TRY(hipEventElapsedTime(&t, e0, e1));
-  ms[0] = (double)t / ((double)launches * chunk);
   const IterArgs<T> p = c->iter_args<T>();
+  {
+    const bool resident = c->res.G && cg_cap == 0;  // as a solve runs them
+    std::unique_ptr<ResHold> hold(resident ? new ResHold(c->res.G) : nullptr);
+    auto chunk_once = [&](int first) -> int {
+      if (resident)
+        return launch_resident<T>(p, c->res, c->res_matrix<T>(), c->res_x, (ResHost *)c->flags_host, first, chunk, s);
+      POGS_HIP_TRY(hipGraphLaunch(c->graph, s));
+      return POGS_OK;
+    };
+    if ((rc = chunk_once(1))) return rc;  // warm
+    POGS_HIP_TRY(hipEventRecord(e0, s));
+    for (int i = 0; i < launches; ++i)
+      if ((rc = chunk_once(0))) return rc;
+    POGS_HIP_TRY(hipEventRecord(e1, s));
+    POGS_HIP_TRY(hipEventSynchronize(e1));
+    POGS_HIP_TRY(hipEventElapsedTime(&t, e0, e1));
+    if (resident) c->res_epoch += (1u << 20) + 2u * (unsigned)chunk * (unsigned)(launches + 1);
+  }
+  ms[0] = (double)t / ((double)launches * chunk);
   auto part = [&](int w) {
     if (c->sparse) launch_iteration_cg_sparse_part<T>(p, w, s);
     else if (cg_cap > 0) launch_iteration_cg_part<T>(p, w, c->splits, c->rps, c->ncolp, s);
