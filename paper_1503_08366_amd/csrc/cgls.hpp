@@ -8,6 +8,9 @@
 namespace pogs {
 
 
+// Waves of the widest workgroup that runs these prologues.
+constexpr int kCgWaves = 8;
+
 // Sum of `len` partials in a fixed order, returned to every thread of the block.
 __device__ inline double block_total(const double *slots, int len, double *scratch) {
   double t = 0.0;
@@ -57,7 +60,7 @@ template <typename T> struct EpiCgFirst {
 // thr^2 = (cg_tol eps_dual / rho)^2 from this iteration's ||mu_h|| and rho
 // and marks the CGLS running.
 template <typename T> __device__ bool cg_first_enter(const IterArgs<T> &p) {
-  __shared__ double sc[kBlock / kWave];
+  __shared__ double sc[kCgWaves];
   if (p.ctrl->st[p.par].done) return false;
   if (blockIdx.x == 0) {
     const double mu2 = block_total(p.s_mu + (size_t)p.par * p.n_smu, p.n_smu, sc);
@@ -100,7 +103,7 @@ template <typename T> struct EpiCgRows {
 // records where this projection stopped.
 template <typename T>
 __device__ bool cg_rows_enter(const IterArgs<T> &p, int j, int cap, EpiCgRows<T> *e) {
-  __shared__ double sc[kBlock / kWave];
+  __shared__ double sc[kCgWaves];
   Ctrl &q = *p.ctrl;
   if (q.st[p.par].done) return false;
   const int stop = q.cg.stop;
@@ -163,7 +166,7 @@ template <typename T> struct EpiCgStep {
 // ||p_j||^2 = ||s_j||^2 + 2 beta s_j^T p_{j-1} + beta^2 ||p_{j-1}||^2;
 // workgroup 0 stores alpha_j and ||p_j||^2.
 template <typename T> __device__ bool cg_step_enter(const IterArgs<T> &p, int j, EpiCgStep<T> *e) {
-  __shared__ double sc[kBlock / kWave];
+  __shared__ double sc[kCgWaves];
   Ctrl &q = *p.ctrl;
   if (q.st[p.par].done || q.cg.stop >= 0) return false;
   const double qq = block_total(p.s_qq, p.n_pri, sc);

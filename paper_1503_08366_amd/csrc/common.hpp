@@ -104,6 +104,27 @@ __device__ inline double row16_sum_dpp(double v) {
 }
 __device__ inline double half32_sum_dpp(double v) { return swap_pair_sum16(row16_sum_dpp(v)); }
 
+// Two values to one register: the lower 32 lanes keep a's sums over lane
+// pairs 32 apart, the upper ones b's; then the same over rows of 16.
+__device__ __forceinline__ double merge_sum32(double a, double b) {
+  const unsigned long long x = (unsigned long long)__double_as_longlong(a), y = (unsigned long long)__double_as_longlong(b);
+  const auto l = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+  return __longlong_as_double((long long)l[0] | ((long long)h[0] << 32)) +
+         __longlong_as_double((long long)l[1] | ((long long)h[1] << 32));
+}
+__device__ __forceinline__ double merge_sum16(double a, double b) {
+  const unsigned long long x = (unsigned long long)__double_as_longlong(a), y = (unsigned long long)__double_as_longlong(b);
+  const auto l = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+  const auto h = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+  return __longlong_as_double((long long)l[0] | ((long long)h[0] << 32)) +
+         __longlong_as_double((long long)l[1] | ((long long)h[1] << 32));
+}
+// Sums of a, b, c, d over the wave's lanes, in lanes 0-15, 32-47, 16-31 and 48-63.
+__device__ __forceinline__ double wave_sum4(double a, double b, double c, double d) {
+  return row16_sum_dpp(merge_sum16(merge_sum32(a, b), merge_sum32(c, d)));
+}
+
 // Sum over groups of W consecutive lanes (W a power of two <= 64).
 template <int W> __device__ inline double group_sum(double v) {
 #pragma unroll

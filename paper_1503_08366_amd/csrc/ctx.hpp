@@ -274,6 +274,9 @@ struct pogs_ctx {
   int smu_cap = 0, syh_cap = 0;  // s_mu / s_yh slots per parity: max(nbx, n_dual), max(nby, splits, fp_blocks)
   int fp_blocks = 0;   // workgroups of the one-pass kernel (0: the context cannot run it)
   bool fused = false;  // iterations run the one-pass tall launches (set per solve, see IterArgs::fused)
+  int cg_blocks = 0;         // workgroups of the one-pass CGLS launches (0: the context cannot run them)
+  bool cg_one_pass = false;  // CGLS solves run them (set per solve)
+  int pri_cap() const { return std::max({n_pri, fp_blocks, cg_blocks}); }  // slots of s_pri and s_qq
   double ms_setup = 0.0;
   hipGraphExec_t graph = nullptr;
   unsigned *flags_host = nullptr;  // setup flags read back by pogs_init (pinned)
@@ -354,10 +357,11 @@ struct pogs_ctx {
     p.n_syh = fused ? std::max(splits, fp_blocks) : nby;
     p.s_mu = slots;                    // 2 x n_smu (by iteration parity), room for 2 x smu_cap
     p.s_yh = slots + 2 * smu_cap;      // 2 x n_syh, room for 2 x syh_cap
-    p.s_pri = p.s_yh + 2 * syh_cap;    // n_pri, room for max(n_pri, fp_blocks)
-    p.s_dual = p.s_pri + std::max(n_pri, fp_blocks);
+    p.s_pri = p.s_yh + 2 * syh_cap;    // n_pri, room for pri_cap()
+    p.s_dual = p.s_pri + pri_cap();
     p.par = 0;
-    p.n_pri = fused ? fp_blocks : n_pri;
+    p.cg_blocks = cg_one_pass ? cg_blocks : 0;
+    p.n_pri = fused ? fp_blocks : cg_one_pass ? cg_blocks : n_pri;
     p.fp_blocks = fp_blocks;
     p.n_dual = n_dual;
     p.ctrl = ctrl;
@@ -369,7 +373,7 @@ struct pogs_ctx {
     p.s_gam = p.s_dual + n_dual;     // 2 x n_dual
     p.s_sig = p.s_gam + 2 * n_dual;  // 2 x n_dual
     p.s_qq = p.s_sig + 2 * n_dual;   // n_pri
-    p.s_gobj = p.s_qq + n_pri;       // nbx + nby
+    p.s_gobj = p.s_qq + pri_cap();  // nbx + nby
     p.s_gconj = p.s_gobj + nbx + nby;  // nbx + nby
     if (sparse) {
       p.sa = Csr<T>{sp_rp, sp_ci, (T *)sp_va, (int)m, sp_lpr, sp_grid, 1};

@@ -102,6 +102,19 @@ inline int one_pass_blocks(int64_t m, int64_t n, int ld, int elem_size, bool spa
   return (int)std::min<int64_t>(cap, std::max<int64_t>(1, (m + 63) / 64));
 }
 
+// Workgroups of the CGLS passes that read A once (cg_one_pass_body, and
+// cg_group_pass_kernel for rows over 1024 entries), or 0 where they do not apply:
+// one per CU, with at least a turn of rows each (32, and 8).  Rows over 1024
+// entries with fewer than 10 rows per workgroup stay with two passes, whose
+// smaller workgroups start sooner (whole solves in two passes / one: 2000 x 2000
+// 21.4 / 22.0 ms, 3000 x 1500 14.3 / 13.8, 20000 x 2000 24.0 / 16.8, 1000 x 900 15.0 /
+// 12.6, 300 x 100 6.2 / 4.7).
+inline int cg_one_pass_blocks(int64_t m, int64_t n, int ld, int elem_size, bool sparse) {
+  if (elem_size != 4 || sparse || m < n || ld > 2048) return 0;
+  if (ld > 1024 && m < 2560) return 0;
+  return (int)std::min<int64_t>(256, (m + (ld > 1024 ? 7 : 31)) / (ld > 1024 ? 8 : 32));
+}
+
 // Default load policy of the passes over A (when not tuned): a matrix larger
 // than this is streamed with non-temporal loads (the MI355X last-level cache
 // holds 256 MB; below this size A partly stays cached from one pass to the
@@ -145,6 +158,7 @@ template <typename T> struct IterArgs {
   // the first pass, (r1, q) for the CG steps), one gather per entry
   Csr<T> sa, sat;
   T *pair;
+  int cg_blocks;         // workgroups of the CGLS passes that read A once for both products (0: two passes)
   int nt_rows, nt_cols;  // 1: the row passes (A v) / column passes (A^T v) over A load non-temporally
 };
 

@@ -194,8 +194,8 @@ template <typename T> int alloc_iteration(pogs_ctx *c) {
   c->smu_cap = std::max(c->nbx, c->n_dual);
   c->syh_cap = std::max({c->nby, c->splits, c->fp_blocks});
   c->fused = false;
-  const int nslots = 2 * (c->smu_cap + c->syh_cap) + std::max(c->n_pri, c->fp_blocks) + c->n_dual +
-                     4 * c->n_dual + c->n_pri + 2 * (c->nbx + c->nby) + c->nbx + c->nby;
+  c->cg_blocks = cg_one_pass_blocks(m, n, c->ld, (int)sizeof(T), c->sparse);
+  const int nslots = 2 * (c->smu_cap + c->syh_cap) + c->pri_cap() + c->n_dual + 4 * c->n_dual + c->pri_cap() + 2 * (c->nbx + c->nby) + c->nbx + c->nby;
   const int ntiles = (int)cdiv(n, gemv_t_tile(sizeof(T)));
   // raw functions: fh0 | gh0 | f0 | g0, uploaded in one copy
   Carve raw;
@@ -210,7 +210,7 @@ template <typename T> int alloc_iteration(pogs_ctx *c) {
   const size_t o_fh = cv.take(m), o_gh = cv.take(n);
   const size_t o_fs = cv.take((size_t)5 * m * sizeof(T)), o_gs = cv.take((size_t)5 * n * sizeof(T));
   const size_t o_raw = cv.take(c->fn_bytes);
-  const size_t o_part = cv.take((size_t)std::max(c->splits, c->fp_blocks) * 2 * c->ncolp * 8);
+  const size_t o_part = cv.take((size_t)std::max({c->splits, c->fp_blocks, c->cg_blocks}) * 2 * c->ncolp * 8);
   const size_t o_slots = cv.take((size_t)nslots * 8);
   const size_t o_cnt = cv.take((size_t)(ntiles + 64) * sizeof(unsigned));
   const size_t o_ctrl = cv.take(sizeof(Ctrl));
@@ -777,6 +777,7 @@ template <typename T> int solve_impl(pogs_ctx *c, const pogs_fn *f, const pogs_f
   const int chunk = even_chunk(p.chunk_iters);
   auto start = [&](bool fused) -> int {
     c->fused = fused;
+    c->cg_one_pass = cg_cap > 0 && c->cg_blocks > 0;
     // zero state (Algorithm 1 starts from x = y = x~ = y~ = 0), or the warm start
     POGS_HIP_TRY(hipMemsetAsync(c->vec, 0, c->vec_elems() * sizeof(T), s));
     if (x0 || nu0) {
@@ -888,6 +889,7 @@ template <typename T> int profile_impl(pogs_ctx *c, int reps, double *ms) {
   }
   const int cg_cap = c->proj == POGS_PROJ_CGLS ? c->params.cg_max_iter : 0;
   c->fused = c->fp_blocks > 0 && cg_cap == 0;  // the launches of a residual-rule solve
+  c->cg_one_pass = c->cg_blocks > 0 && cg_cap > 0;
   h.cg_tol = c->params.cg_tol;
   h.cg_cap = cg_cap;
   h.cg.stop = -1;

@@ -132,26 +132,6 @@ __device__ __forceinline__ void res_gather(int n, unsigned tag, int *bad, Src sr
   }
 }
 
-// Two values to one register: the lower 32 lanes keep a's sums over lane
-// pairs 32 apart, the upper ones b's; then the same over rows of 16.
-__device__ __forceinline__ double merge_sum32(double a, double b) {
-  const unsigned long long x = (unsigned long long)__double_as_longlong(a), y = (unsigned long long)__double_as_longlong(b);
-  const auto l = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
-  const auto h = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
-  return __longlong_as_double((long long)l[0] | ((long long)h[0] << 32)) +
-         __longlong_as_double((long long)l[1] | ((long long)h[1] << 32));
-}
-__device__ __forceinline__ double merge_sum16(double a, double b) {
-  const unsigned long long x = (unsigned long long)__double_as_longlong(a), y = (unsigned long long)__double_as_longlong(b);
-  const auto l = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
-  const auto h = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
-  return __longlong_as_double((long long)l[0] | ((long long)h[0] << 32)) +
-         __longlong_as_double((long long)l[1] | ((long long)h[1] << 32));
-}
-// Sums of a, b, c, d over the wave's lanes, in lanes 0-15, 32-47, 16-31 and 48-63.
-__device__ __forceinline__ double wave_sum4(double a, double b, double c, double d) {
-  return row16_sum_dpp(merge_sum16(merge_sum32(a, b), merge_sum32(c, d)));
-}
 __device__ __forceinline__ double lane_value(double v, int l) {  // l uniform
   const unsigned long long b = (unsigned long long)__double_as_longlong(v);
   const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, l);
