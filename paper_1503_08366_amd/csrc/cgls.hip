@@ -39,14 +39,16 @@ template <typename T>
 __global__ __launch_bounds__(kBlock) void cg_first_finish_kernel(IterArgs<T> p, int splits, int ncolp) {
   if (!cg_first_enter<T>(p)) return;
   EpiCgFirst<T> e{p};
-  gemv_t_finish_body<2, EpiCgFirst<T>>(hw_block(), p.n, splits, p.part, ncolp, e);
+  __shared__ GemvFinishLds lds;
+  gemv_t_finish_body<2, EpiCgFirst<T>>(hw_block(), p.n, splits, p.part, ncolp, e, lds);
 }
 
 template <typename T>
 __global__ __launch_bounds__(kBlock) void cg_finish_kernel(IterArgs<T> p, int j, int splits, int ncolp) {
   EpiCgStep<T> e;
   if (!cg_step_enter<T>(p, j, &e)) return;
-  gemv_t_finish_body<2, EpiCgStep<T>>(hw_block(), p.n, splits, p.part, ncolp, e);
+  __shared__ GemvFinishLds lds;
+  gemv_t_finish_body<2, EpiCgStep<T>>(hw_block(), p.n, splits, p.part, ncolp, e, lds);
 }
 
 // One pass over A for both products of a CG step (or, FIRST, of the passes that
@@ -396,7 +398,8 @@ template <typename T, int LPR, int RPT, bool NT>
 __global__ __launch_bounds__(kBlock) void cg_rows_lds_kernel(IterArgs<T> p, int j, int cap) {
   EpiCgRows<T> e;
   if (!cg_rows_enter<T>(p, j, cap, &e)) return;
-  gemv_n_body<T, T, 1, false, LPR, RPT, EpiCgRows<T>, NT>(hw_block(), p.A, p.m, p.n, p.ld, p.sv, p.sv, e);
+  __shared__ GemvNLds<T, 1> lds;
+  gemv_n_body<T, T, 1, false, LPR, RPT, EpiCgRows<T>, NT>(hw_block(), p.A, p.m, p.n, p.ld, p.sv, p.sv, e, lds);
 }
 
 template <typename T, bool NT> static void launch_cg_rows_nt(const IterArgs<T> &p, int j, int cap, hipStream_t s) {

@@ -48,14 +48,21 @@ template <bool SQUARE> __device__ inline double elem_op(double a) {
 //   void tile_done(int tile, double sum)       -> thread 0 of the tile's workgroup
 // The finish kernel also accepts column() returning Sum2 (two values summed
 // per tile) with tile_done(int tile, double sum_a, double sum_b).
+// Each body takes its LDS from the kernel, so that a kernel which runs one of
+// several bodies per workgroup holds the largest of them and not their sum.
+template <typename TA, int NRHS> struct GemvTLds {
+  double red[4][NRHS][kWave * Vec16<TA>::N];
+};
+
 template <typename TA, typename TV, int NRHS, bool SQUARE, class Epi, bool NT = false>
 __device__ __forceinline__ void gemv_t_body(
     const Blk &b, const TA *__restrict__ A, int m, int n, int ld, const TV *__restrict__ v0,
-    const TV *__restrict__ v1, int rows_per_split, double *__restrict__ part, int ncolp, const Epi &epi) {
+    const TV *__restrict__ v1, int rows_per_split, double *__restrict__ part, int ncolp, const Epi &epi,
+    GemvTLds<TA, NRHS> &lds) {
   using V = typename Vec16<TA>::type;
   constexpr int VN = Vec16<TA>::N;
   constexpr int TILE = kWave * VN;
-  __shared__ double red[4][NRHS][TILE];
+  auto &red = lds.red;
   const bool stopped = epi.skip();  // used once the first group's loads are out
 
   const int lane = threadIdx.x & (kWave - 1);
@@ -142,7 +149,8 @@ __global__ __launch_bounds__(kBlock) void gemv_t_kernel(const TA *__restrict__ A
                                                         const TV *__restrict__ v0, const TV *__restrict__ v1,
                                                         int rows_per_split, double *__restrict__ part, int ncolp,
                                                         Epi epi) {
-  gemv_t_body<TA, TV, NRHS, SQUARE, Epi, NT>(hw_block(), A, m, n, ld, v0, v1, rows_per_split, part, ncolp, epi);
+  __shared__ GemvTLds<TA, NRHS> lds;
+  gemv_t_body<TA, TV, NRHS, SQUARE, Epi, NT>(hw_block(), A, m, n, ld, v0, v1, rows_per_split, part, ncolp, epi, lds);
 }
 
 // Sum the split partials of kFinishCols columns (block b.x): the threads
@@ -150,12 +158,17 @@ __global__ __launch_bounds__(kBlock) void gemv_t_kernel(const TA *__restrict__ A
 // g + groups, ...; the group sums are then added in group order (a fixed
 // order, so results are deterministic); each column is finished by the
 // epilogue and the block's sum goes to tile_done(b.x, .).
+struct GemvFinishLds {
+  double red[kBlock / kFinishCols][2][kFinishCols];
+  double bs[kBlock / kWave];
+};
+
 template <int NRHS, class Epi>
 __device__ __forceinline__ void gemv_t_finish_body(const Blk &b, int n, int splits, const double *__restrict__ part,
-                                                   int ncolp, const Epi &epi) {
+                                                   int ncolp, const Epi &epi, GemvFinishLds &lds) {
   constexpr int G = kBlock / kFinishCols;
-  __shared__ double red[G][2][kFinishCols];
-  __shared__ double bs[kBlock / kWave];
+  auto &red = lds.red;
+  auto &bs = lds.bs;
   const bool stopped = epi.skip();  // used once the partial loads are out
   const int c = threadIdx.x % kFinishCols;
   const int g = threadIdx.x / kFinishCols;
@@ -195,7 +208,8 @@ __device__ __forceinline__ void gemv_t_finish_body(const Blk &b, int n, int spli
 template <int NRHS, class Epi>
 __global__ __launch_bounds__(kBlock) void gemv_t_finish_kernel(int n, int splits, const double *__restrict__ part,
                                                                 int ncolp, Epi epi) {
-  gemv_t_finish_body<NRHS, Epi>(hw_block(), n, splits, part, ncolp, epi);
+  __shared__ GemvFinishLds lds;
+  gemv_t_finish_body<NRHS, Epi>(hw_block(), n, splits, part, ncolp, epi, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -207,18 +221,22 @@ __global__ __launch_bounds__(kBlock) void gemv_t_finish_kernel(int n, int splits
 //                                             summed per workgroup
 //   void block_done(int block, double sum)   -> thread 0 of each workgroup
 template <typename TV> struct GemvNChunk { static constexpr int value = 8192 / sizeof(TV) * 2; };
+template <typename TV, int NRHS> struct GemvNLds {
+  TV vs[NRHS][GemvNChunk<TV>::value];
+  double bs[kBlock / kWave];
+};
 
 template <typename TA, typename TV, int NRHS, bool SQUARE, int LPR, int RPT, class Epi, bool NT = false>
 __device__ __forceinline__ void gemv_n_body(
     const Blk &b, const TA *__restrict__ A, int m, int n, int ld, const TV *__restrict__ v0,
-    const TV *__restrict__ v1, const Epi &epi) {
+    const TV *__restrict__ v1, const Epi &epi, GemvNLds<TV, NRHS> &lds) {
   using V = typename Vec16<TA>::type;
   constexpr int VN = Vec16<TA>::N;
   constexpr int CH = GemvNChunk<TV>::value;  // vector elements staged per chunk
   constexpr int GPW = kWave / LPR;            // row groups per wave
   constexpr int ROWS = (kBlock / kWave) * GPW * RPT;
-  __shared__ TV vs[NRHS][CH];
-  __shared__ double bs[kBlock / kWave];
+  auto &vs = lds.vs;
+  auto &bs = lds.bs;
   if (epi.skip()) return;
 
   const int lane = threadIdx.x & (kWave - 1);
@@ -306,7 +324,8 @@ template <typename TA, typename TV, int NRHS, bool SQUARE, int LPR, int RPT, cla
 __global__ __launch_bounds__(kBlock) void gemv_n_kernel(const TA *__restrict__ A, int m, int n, int ld,
                                                         const TV *__restrict__ v0, const TV *__restrict__ v1,
                                                         Epi epi) {
-  gemv_n_body<TA, TV, NRHS, SQUARE, LPR, RPT, Epi, NT>(hw_block(), A, m, n, ld, v0, v1, epi);
+  __shared__ GemvNLds<TV, NRHS> lds;
+  gemv_n_body<TA, TV, NRHS, SQUARE, LPR, RPT, Epi, NT>(hw_block(), A, m, n, ld, v0, v1, epi, lds);
 }
 
 // ---------------------------------------------------------------------------

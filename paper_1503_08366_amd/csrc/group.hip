@@ -72,7 +72,8 @@ __device__ __forceinline__ EqArgs eq_args(const GProb &P) {
 __global__ __launch_bounds__(kBlock) void g_eq_colfinish(const GProb *probs, const GItem *items) {
   GROUP_ITEM();
   EpiEqCol e{eq_args(P)};
-  gemv_t_finish_body<1, EpiEqCol>(b, P.it.n, P.eq_nsplit, P.eq_part, P.eq_ncolp, e);
+  __shared__ GemvFinishLds lds;
+  gemv_t_finish_body<1, EpiEqCol>(b, P.it.n, P.eq_nsplit, P.eq_part, P.eq_ncolp, e, lds);
 }
 
 __global__ __launch_bounds__(256) void g_eq_normalize(const GProb *probs, const GItem *items) {
@@ -176,28 +177,6 @@ __global__ __launch_bounds__(kBlock) void g_prox(const GProb *probs, const GItem
   prox_body<float, false, true>(b, iter_args(P, par));
 }
 
-__global__ __launch_bounds__(kBlock) void g_pass1_t(const GProb *probs, const GItem *items, int par) {
-  GROUP_ITEM();
-  const IterArgs<float> p = iter_args(P, par);
-  EpiTallPass1<float> e{{p}};
-  gemv_t_body<float, float, 2, false>(b, p.A, p.m, p.n, p.ld, p.dy, p.nu, P.rps, p.part, P.ncolp, e);
-}
-
-template <int LPR, int RPT>
-__global__ __launch_bounds__(kBlock) void g_pass1_w(const GProb *probs, const GItem *items, int par) {
-  GROUP_ITEM();
-  const IterArgs<float> p = iter_args(P, par);
-  EpiWidePass1<float> e{{p}};
-  gemv_n_body<float, float, 2, false, LPR, RPT>(b, p.A, p.m, p.n, p.ld, p.cx, p.xh, e);
-}
-
-__global__ __launch_bounds__(kBlock) void g_finish1(const GProb *probs, const GItem *items, int par) {
-  GROUP_ITEM();
-  const IterArgs<float> p = iter_args(P, par);
-  EpiTallPass1<float> e{{p}};
-  gemv_t_finish_body<2>(b, p.n, P.splits, p.part, P.ncolp, e);
-}
-
 // The solve's epilogue for either orientation (chosen per problem).
 struct EpiSolveAny {
   IterArgs<float> p;
@@ -218,34 +197,84 @@ struct EpiSolveAny {
   __device__ void block_done(int, double) const {}
 };
 
-template <int LPR, int RPT>
-__global__ __launch_bounds__(kBlock) void g_solve(const GProb *probs, const GItem *items, int par) {
-  GROUP_ITEM();
-  const IterArgs<float> p = iter_args(P, par);
-  EpiSolveAny e{p, P.tall};
-  gemv_n_body<float, float, 1, false, LPR, RPT>(b, p.Kinv, p.q, p.q, p.ldk, p.rhs, p.rhs, e);
+// The four steps of an iteration after the prox step.  A tall problem goes
+// through column sums, their finish, the solve and the row dots; a wide one
+// through row dots, the solve, column sums and their finish.  The two chains
+// are equally long and independent, so step k of both, and both widths of a
+// row pass, share a launch: the workgroup picks its body by its problem's
+// shape.  An iteration of a mixed group is 5 launches; with a launch per body
+// it was 11, and the small ones (4 to 9 us each, a fraction of the chip) ran
+// one after another (32 mixed problems up to 4096 x 1024, whole batch: 30.4 ->
+// 25.1 ms).  The bodies share one LDS block.
+union StepLds {
+  GemvTLds<float, 2> t;
+  GemvFinishLds f;
+  GemvNLds<float, 2> n2;
+  GemvNLds<float, 1> n1;
+};
+
+template <class Epi>
+__device__ __forceinline__ void rows_of_a(const Blk &b, const GProb &P, const IterArgs<float> &p, const float *v0,
+                                          const float *v1, const Epi &e, GemvNLds<float, 2> &lds) {
+  if (P.lpr16) gemv_n_body<float, float, 2, false, 16, 4>(b, p.A, p.m, p.n, p.ld, v0, v1, e, lds);
+  else gemv_n_body<float, float, 2, false, 64, 4>(b, p.A, p.m, p.n, p.ld, v0, v1, e, lds);
 }
 
-template <int LPR, int RPT>
-__global__ __launch_bounds__(kBlock) void g_pass2_t(const GProb *probs, const GItem *items, int par) {
-  GROUP_ITEM();
-  const IterArgs<float> p = iter_args(P, par);
-  EpiTallPass2<float> e{{p}};
-  gemv_n_body<float, float, 2, false, LPR, RPT>(b, p.A, p.m, p.n, p.ld, p.x, p.xh, e);
+__device__ __forceinline__ void solve_rows(const Blk &b, const GProb &P, const IterArgs<float> &p, int tall,
+                                           GemvNLds<float, 1> &lds) {
+  EpiSolveAny e{p, tall};
+  if (P.lpr16k) gemv_n_body<float, float, 1, false, 16, 4>(b, p.Kinv, p.q, p.q, p.ldk, p.rhs, p.rhs, e, lds);
+  else gemv_n_body<float, float, 1, false, 64, 4>(b, p.Kinv, p.q, p.q, p.ldk, p.rhs, p.rhs, e, lds);
 }
 
-__global__ __launch_bounds__(kBlock) void g_pass2_w(const GProb *probs, const GItem *items, int par) {
+__global__ __launch_bounds__(kBlock) void g_step1(const GProb *probs, const GItem *items, int par) {
   GROUP_ITEM();
+  __shared__ StepLds lds;
   const IterArgs<float> p = iter_args(P, par);
-  EpiWidePass2<float> e{{p}};
-  gemv_t_body<float, float, 2, false>(b, p.A, p.m, p.n, p.ld, p.yt, p.nu, P.rps, p.part, P.ncolp, e);
+  if (P.tall) {
+    EpiTallPass1<float> e{{p}};
+    gemv_t_body<float, float, 2, false>(b, p.A, p.m, p.n, p.ld, p.dy, p.nu, P.rps, p.part, P.ncolp, e, lds.t);
+  } else {
+    EpiWidePass1<float> e{{p}};
+    rows_of_a(b, P, p, p.cx, p.xh, e, lds.n2);
+  }
 }
 
-__global__ __launch_bounds__(kBlock) void g_finish2(const GProb *probs, const GItem *items, int par) {
+__global__ __launch_bounds__(kBlock) void g_step2(const GProb *probs, const GItem *items, int par) {
   GROUP_ITEM();
+  __shared__ StepLds lds;
   const IterArgs<float> p = iter_args(P, par);
-  EpiWidePass2<float> e{{p}};
-  gemv_t_finish_body<2>(b, p.n, P.splits, p.part, P.ncolp, e);
+  if (P.tall) {
+    EpiTallPass1<float> e{{p}};
+    gemv_t_finish_body<2>(b, p.n, P.splits, p.part, P.ncolp, e, lds.f);
+  } else {
+    solve_rows(b, P, p, 0, lds.n1);
+  }
+}
+
+__global__ __launch_bounds__(kBlock) void g_step3(const GProb *probs, const GItem *items, int par) {
+  GROUP_ITEM();
+  __shared__ StepLds lds;
+  const IterArgs<float> p = iter_args(P, par);
+  if (P.tall) {
+    solve_rows(b, P, p, 1, lds.n1);
+  } else {
+    EpiWidePass2<float> e{{p}};
+    gemv_t_body<float, float, 2, false>(b, p.A, p.m, p.n, p.ld, p.yt, p.nu, P.rps, p.part, P.ncolp, e, lds.t);
+  }
+}
+
+__global__ __launch_bounds__(kBlock) void g_step4(const GProb *probs, const GItem *items, int par) {
+  GROUP_ITEM();
+  __shared__ StepLds lds;
+  const IterArgs<float> p = iter_args(P, par);
+  if (P.tall) {
+    EpiTallPass2<float> e{{p}};
+    rows_of_a(b, P, p, p.x, p.xh, e, lds.n2);
+  } else {
+    EpiWidePass2<float> e{{p}};
+    gemv_t_finish_body<2>(b, p.n, P.splits, p.part, P.ncolp, e, lds.f);
+  }
 }
 
 __global__ __launch_bounds__(kBlock) void g_preview(const GProb *probs, const GItem *items, int par) {
@@ -325,16 +354,10 @@ void launch_group(int phase, const GProb *probs, const GItem *items, int count, 
     case G_UPDATE: hipLaunchKernelGGL(g_update, grid, blk, 0, s, probs, items, arg); break;
     case G_KINV: hipLaunchKernelGGL(g_kinv, grid, blk, 0, s, probs, items); break;
     case G_PROX: hipLaunchKernelGGL(g_prox, grid, blk, 0, s, probs, items, arg); break;
-    case G_PASS1_T: hipLaunchKernelGGL(g_pass1_t, grid, blk, 0, s, probs, items, arg); break;
-    case G_PASS1_W64: hipLaunchKernelGGL((g_pass1_w<64, 4>), grid, blk, 0, s, probs, items, arg); break;
-    case G_PASS1_W16: hipLaunchKernelGGL((g_pass1_w<16, 4>), grid, blk, 0, s, probs, items, arg); break;
-    case G_FINISH1: hipLaunchKernelGGL(g_finish1, grid, blk, 0, s, probs, items, arg); break;
-    case G_SOLVE64: hipLaunchKernelGGL((g_solve<64, 4>), grid, blk, 0, s, probs, items, arg); break;
-    case G_SOLVE16: hipLaunchKernelGGL((g_solve<16, 4>), grid, blk, 0, s, probs, items, arg); break;
-    case G_PASS2_T64: hipLaunchKernelGGL((g_pass2_t<64, 4>), grid, blk, 0, s, probs, items, arg); break;
-    case G_PASS2_T16: hipLaunchKernelGGL((g_pass2_t<16, 4>), grid, blk, 0, s, probs, items, arg); break;
-    case G_PASS2_W: hipLaunchKernelGGL(g_pass2_w, grid, blk, 0, s, probs, items, arg); break;
-    case G_FINISH2: hipLaunchKernelGGL(g_finish2, grid, blk, 0, s, probs, items, arg); break;
+    case G_STEP1: hipLaunchKernelGGL(g_step1, grid, blk, 0, s, probs, items, arg); break;
+    case G_STEP2: hipLaunchKernelGGL(g_step2, grid, blk, 0, s, probs, items, arg); break;
+    case G_STEP3: hipLaunchKernelGGL(g_step3, grid, blk, 0, s, probs, items, arg); break;
+    case G_STEP4: hipLaunchKernelGGL(g_step4, grid, blk, 0, s, probs, items, arg); break;
     case G_PREVIEW: hipLaunchKernelGGL(g_preview, grid, blk, 0, s, probs, items, arg); break;
     case G_UNSCALE: hipLaunchKernelGGL(g_unscale, grid, blk, 0, s, probs, items); break;
     case G_INIT_STATE: hipLaunchKernelGGL(g_init_state, grid, dim3(64), 0, s, probs, items); break;

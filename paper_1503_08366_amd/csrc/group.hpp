@@ -71,16 +71,10 @@ enum GPhase : int {
   G_UPDATE,           // Cholesky / inverse step, second half (arg: kb)
   G_KINV,             // K^{-1} = L^{-T} L^{-1} in float32
   G_PROX,             // prox step (+ stop test of the previous iteration); arg: parity for all below
-  G_PASS1_T,          // tall: A^T [d, nu_h] split partials
-  G_PASS1_W64,        // wide: A [c, x_h], 64 lanes per row
-  G_PASS1_W16,        // wide: A [c, x_h], 16 lanes per row
-  G_FINISH1,          // tall: column finish of pass 1
-  G_SOLVE64,          // K^{-1} rhs, 64 lanes per row
-  G_SOLVE16,          // K^{-1} rhs, 16 lanes per row
-  G_PASS2_T64,        // tall: A [x, x_h], 64 lanes per row
-  G_PASS2_T16,        // tall: A [x, x_h], 16 lanes per row
-  G_PASS2_W,          // wide: A^T [y~, nu_h] split partials
-  G_FINISH2,          // wide: column finish of pass 2
+  G_STEP1,            // tall: A^T [d, nu_h] split partials; wide: A [c, x_h]
+  G_STEP2,            // tall: column finish of step 1; wide: K^{-1} rhs
+  G_STEP3,            // tall: K^{-1} rhs; wide: A^T [y~, nu_h] split partials
+  G_STEP4,            // tall: A [x, x_h]; wide: column finish of step 3
   G_PREVIEW,          // stop test of the last iteration of a chunk
   G_UNSCALE,          // original variables and objective
   G_INIT_STATE,       // control block for the first iteration

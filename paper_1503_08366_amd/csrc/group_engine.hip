@@ -517,7 +517,7 @@ int GroupEngine::run_chunk(const std::vector<int> &handles, int chunk) {
   if (int rc0 = flush_descriptors()) return rc0;
   chunk += chunk & 1;  // even: the state after the chunk is in st[0]
   const std::vector<int> hs = by_size(probs_, handles);
-  enum { PROX, P1T, P1W64, P1W16, FIN1, SOL64, SOL16, P2T64, P2T16, P2W, FIN2, PREV, NLIST };
+  enum { PROX, STEP1, STEP2, STEP3, STEP4, PREV, NLIST };
   std::vector<std::vector<GItem>> lists(NLIST);
   for (int h : hs) {
     const GProb &P = probs_[h];
@@ -525,16 +525,10 @@ int GroupEngine::run_chunk(const std::vector<int> &handles, int chunk) {
     push_range(lists[PROX], h, g.nbx + g.nby);
     const int rows_a = (int)cdiv(g.m, g.lpr16 ? kGRows16 : kGRows64);
     const int rows_k = (int)cdiv(g.q, g.lpr16k ? kGRows16 : kGRows64);
-    if (g.tall) {
-      push_range(lists[P1T], h, g.tiles, g.splits);
-      push_range(lists[FIN1], h, g.n_dual);
-      push_range(lists[g.lpr16 ? P2T16 : P2T64], h, rows_a);
-    } else {
-      push_range(lists[g.lpr16 ? P1W16 : P1W64], h, rows_a);
-      push_range(lists[P2W], h, g.tiles, g.splits);
-      push_range(lists[FIN2], h, g.n_dual);
-    }
-    push_range(lists[g.lpr16k ? SOL16 : SOL64], h, rows_k);
+    push_range(lists[STEP1], h, g.tall ? g.tiles : rows_a, g.tall ? g.splits : 1);
+    push_range(lists[STEP2], h, g.tall ? g.n_dual : rows_k);
+    push_range(lists[STEP3], h, g.tall ? rows_k : g.tiles, g.tall ? 1 : g.splits);
+    push_range(lists[STEP4], h, g.tall ? rows_a : g.n_dual);
     push_range(lists[PREV], h, 1);
   }
   std::vector<const GItem *> ptr;
@@ -546,16 +540,10 @@ int GroupEngine::run_chunk(const std::vector<int> &handles, int chunk) {
   for (int i = 0; i < chunk; ++i) {
     const int par = i & 1;
     go(G_PROX, PROX, par);
-    go(G_PASS1_T, P1T, par);
-    go(G_PASS1_W64, P1W64, par);
-    go(G_PASS1_W16, P1W16, par);
-    go(G_FINISH1, FIN1, par);
-    go(G_SOLVE64, SOL64, par);
-    go(G_SOLVE16, SOL16, par);
-    go(G_PASS2_T64, P2T64, par);
-    go(G_PASS2_T16, P2T16, par);
-    go(G_PASS2_W, P2W, par);
-    go(G_FINISH2, FIN2, par);
+    go(G_STEP1, STEP1, par);
+    go(G_STEP2, STEP2, par);
+    go(G_STEP3, STEP3, par);
+    go(G_STEP4, STEP4, par);
   }
   go(G_PREVIEW, PREV, 1);
   POGS_HIP_TRY(hipGetLastError());
