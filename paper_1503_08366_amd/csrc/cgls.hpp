@@ -9,7 +9,7 @@ namespace pogs {
 
 
 // Waves of the widest workgroup that runs these prologues.
-constexpr int kCgWaves = 8;
+constexpr int kCgWaves = 16;
 
 // Sum of `len` partials in a fixed order, returned to every thread of the block.
 __device__ inline double block_total(const double *slots, int len, double *scratch) {
@@ -100,8 +100,9 @@ template <typename T> struct EpiCgRows {
 // Start of KA (every thread): false when step j does not run.  The step runs
 // while j < cap and ||s_j||^2 > thr^2; the first KA that finds it does not
 // applies the pending r1 update of step j - 1 (grid-stride over the rows) and
-// records where this projection stopped.
-template <typename T>
+// records where this projection stopped.  PENDING = false: r1 is updated
+// within its step and nothing is left over.
+template <typename T, bool PENDING = true>
 __device__ bool cg_rows_enter(const IterArgs<T> &p, int j, int cap, EpiCgRows<T> *e) {
   __shared__ double sc[kCgWaves];
   Ctrl &q = *p.ctrl;
@@ -112,7 +113,7 @@ __device__ bool cg_rows_enter(const IterArgs<T> &p, int j, int cap, EpiCgRows<T>
   const double alpha_prev = j > 0 ? q.cg.alpha : 0.0;
   const double thr2 = q.cg.thr2;
   if (!(j < cap && gam > thr2)) {
-    if (j > 0)
+    if (PENDING && j > 0)
       for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < p.m; i += gridDim.x * blockDim.x)
         p.yt[i] = (T)((double)p.yt[i] - alpha_prev * (double)p.qv[i]);
     if (blockIdx.x == 0 && threadIdx.x == 0) {

@@ -253,6 +253,7 @@ struct pogs_ctx {
   int sp_lpr = 0, sp_grid = 0, sp_lprt = 0, sp_gridt = 0;
   int sp_nseg = 1;  // column segments of the A^T copy
   void *sp_pair = nullptr;  // 2 m entries of T
+  SpPieces sp_pa{}, sp_pat{};  // the same in pieces (float32, large)
   double *D = nullptr, *E = nullptr;
   // iteration state (T): x y xt yt xh yh mu nu cx dy rhs, outputs xo yo muo nuo
   void *vec = nullptr;
@@ -379,6 +380,8 @@ struct pogs_ctx {
       p.sa = Csr<T>{sp_rp, sp_ci, (T *)sp_va, (int)m, sp_lpr, sp_grid, 1};
       p.sat = Csr<T>{sp_rpt, sp_cit, (T *)sp_vat, (int)n, sp_lprt, sp_gridt, sp_nseg};
       p.pair = (T *)sp_pair;
+      p.pa = sp_pa;
+      p.pat = sp_pat;
     }
     return p;
   }

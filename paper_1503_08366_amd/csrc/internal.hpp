@@ -86,6 +86,23 @@ constexpr size_t kSegBytes = (size_t)1 << 20;
 constexpr int kSegRows = 512;
 constexpr int kSegGrid = 2048;
 
+// A sparse float32 matrix split by columns into nseg segments of seg columns,
+// as many as fit in a workgroup's LDS (pieces.hip): the entries of row r in
+// segment s are [rp[s rows + r], rp[s rows + r + 1]) of va and of ci, ci the
+// column inside its segment.  A workgroup takes `tile` rows and one of `groups`
+// equal runs of segments.  rp == nullptr: the context has no such copy.
+constexpr int kPcWaves = 16;                 // waves of a workgroup
+constexpr int kPcRpl = 8;                    // rows per lane at most
+constexpr int kPcTile = kPcWaves * 64 * kPcRpl;
+constexpr int kPcSeg = 32128;                // columns per segment at most
+constexpr int kPcPad = 256;                  // entries that may be read past the last
+struct SpPieces {
+  int *rp;
+  uint16_t *ci;
+  float *va;
+  int rows, cols, seg, nseg, tile, tiles, groups;
+};
+
 // Workgroups of the one-pass tall iteration (tall_one_pass_body) for an m x n
 // matrix with leading dimension ld, or 0 where it does not apply (not float32,
 // m < n, rows longer than 2048 entries, sparse, or rows over 1024 entries and
@@ -158,6 +175,7 @@ template <typename T> struct IterArgs {
   // the first pass, (r1, q) for the CG steps), one gather per entry
   Csr<T> sa, sat;
   T *pair;
+  SpPieces pa, pat;      // the same two matrices in pieces
   int cg_blocks;         // workgroups of the CGLS passes that read A once for both products (0: two passes)
   int nt_rows, nt_cols;  // 1: the row passes (A v) / column passes (A^T v) over A load non-temporally
 };
@@ -272,10 +290,21 @@ void sparse_seg_shape(int rows, int nseg, int64_t nnz, int *lpr, int *grid);
 template <typename T>
 void run_equilibrate_sparse(Csr<T> A, Csr<T> At, int m, int n, int iters, double eps_cmp, double *D, double *E,
                             double *ws, hipStream_t s);
+// The copies in pieces (pieces.hip).  pieces_shape: false where the row
+// passes over the plain copy are used instead.  fill_pieces: rp, ci and va of
+// P from the scaled A; cur holds nseg rows int, sums pieces_sums(P) int.
+// launch_pc_*: the passes of a projection (start, one CG step, its rows alone).
+bool pieces_shape(int64_t rows, int64_t cols, int64_t nnz, int groups, SpPieces *P);
+int64_t pieces_sums(const SpPieces &P);
+void fill_pieces(const Csr<float> &A, const SpPieces &P, int64_t nnz, int *cur, int *sums, hipStream_t s);
+int pieces_finish_blocks(int n);
+void launch_pc_first(const IterArgs<float> &p, int ncolp, hipStream_t s);
+void launch_pc_rows(const IterArgs<float> &p, int j, int cap, hipStream_t s);
+void launch_pc_step(const IterArgs<float> &p, int j, int cap, int ncolp, hipStream_t s);
 // One iteration with the CGLS projection on the sparse pair (two launches per CG step).
-template <typename T> void launch_iteration_cg_sparse(const IterArgs<T> &p, int cap, hipStream_t s);
+template <typename T> void launch_iteration_cg_sparse(const IterArgs<T> &p, int cap, int ncolp, hipStream_t s);
 // Parts for the profiler: 0 prox, 1 first passes, 2 one CG step.
-template <typename T> void launch_iteration_cg_sparse_part(const IterArgs<T> &p, int which, hipStream_t s);
+template <typename T> void launch_iteration_cg_sparse_part(const IterArgs<T> &p, int which, int ncolp, hipStream_t s);
 // Warm start on the sparse pair: the state the dense warm start sets, with
 // y = A^ x and x~ = -A^T y~ as row passes over A^ and A^T.
 template <typename T>

@@ -1,0 +1,422 @@
+// Passes over a large sparse float32 matrix kept in pieces: split by columns
+// into segments of at most kPcSeg, so that the part of the vector a segment
+// multiplies is in the workgroup's LDS and every gather is an LDS read.
+//
+// A row pass that gathers from L2 ran at 130 G gathers/s on gfx950 (245 us for
+// the 32 M entries of a 2000000 x 200000 matrix, and no faster with more rows
+// in flight): each 4-byte gather moves a 128-byte line through a CU's L1, while
+// the entries themselves need 50 us of HBM.
+//
+// Measured, 2000000 x 200000, 16 entries a row: A^ s 245 -> 76 us, A^T r1 255
+// -> 85 (the entries, row bounds and partial sums are 280 and 300 MB), a CG step
+// 500 -> 188, a Lasso 336 -> 147 ms.  Of a pass, adding up the products takes
+// about 12 us, refilling the segments 5, the gathers 2.  Two groups of entries on
+// the way: 1 and 3 are 1 and 6 % slower (3 runs out of registers).
+//
+// A workgroup (16 waves, one per CU: the segment takes most of the LDS) owns
+// up to kPcTile rows; a wave takes 64 of them at a time, one per lane, for each
+// segment in turn.  The entries of 64 rows in one segment are contiguous, so
+// the wave loads them with 16-byte loads, 4 per lane, multiplies each by its
+// element of the segment and lays the float64 products out in LDS, where each
+// lane then adds up its own row's.  The rows' sums stay in registers over the
+// segments.  The next 64 rows' entries are loaded before these are added up.
+//
+// A^ (more rows than columns): a workgroup goes through all segments and ends
+// with the rows' epilogue.  A^T: few long rows, so its segments are dealt to
+// kGroups workgroups per row range, whose float64 sums a finish kernel adds in
+// order.  The column index inside a segment takes 16 bits: 6 bytes per entry
+// instead of 8.
+#include "cgls.hpp"
+
+namespace pogs {
+
+namespace {
+
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef unsigned short u4 __attribute__((ext_vector_type(4)));
+typedef double d2 __attribute__((ext_vector_type(2)));
+
+constexpr int kPcThreads = kPcWaves * 64;
+constexpr int kPcChunk = 256;  // entries a wave handles at once, 4 per lane
+constexpr int kPcSegLoads = (kPcSeg + 4 * kPcThreads - 1) / (4 * kPcThreads);
+constexpr int kPcAhead = 2;    // groups of 64 rows whose entries are on the way
+constexpr int kPcWg = 256;     // workgroups of a launch that fill the GPU
+
+struct PcLds {
+  float v[kPcSeg];
+  double prod[kPcWaves][kPcChunk + 4];  // the sums read up to 3 past their last product
+};
+
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// acc[g] = row (first row of the tile) + (16 g + wave) 64 + lane times the
+// vector, over the segments sg0 .. sg1 - 1; src(i) returns elements i .. i + 3.
+template <class Src>
+__device__ __forceinline__ void pieces_body(const SpPieces &A, int tile, int sg0, int sg1, const Src &src, PcLds &lds,
+                                            double (&acc)[kPcRpl]) {
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r0 = tile * A.tile, r1 = min(A.rows, r0 + A.tile);
+  double *pw = lds.prod[w];
+#pragma unroll
+  for (int g = 0; g < kPcRpl; ++g) acc[g] = 0.0;
+  for (int sg = sg0; sg < sg1; ++sg) {
+    const int c0 = sg * A.seg, len = min(A.seg, A.cols - c0);
+    const int *rp = A.rp + (size_t)sg * A.rows;
+    f4 st[kPcSegLoads];
+#pragma unroll
+    for (int u = 0; u < kPcSegLoads; ++u) {
+      const int t = (u * kPcThreads + threadIdx.x) * 4;
+      if (t < len) st[u] = src(c0 + t);
+    }
+    // where every row's entries begin (lanes past the last row: where it ends);
+    // a lane's entries end where the next lane's begin
+    int lo[kPcRpl], ends[kPcRpl];
+#pragma unroll
+    for (int g = 0; g < kPcRpl; ++g) {
+      const int rb = r0 + (g * kPcWaves + w) * 64;
+      lo[g] = rp[min(rb + lane, r1)];
+      ends[g] = rp[min(rb + 64, r1)];
+    }
+    __syncthreads();  // the last segment has been read
+#pragma unroll
+    for (int u = 0; u < kPcSegLoads; ++u) {
+      const int t = (u * kPcThreads + threadIdx.x) * 4;
+      if (t < len) *reinterpret_cast<f4 *>(lds.v + t) = st[u];
+    }
+    f4 a[kPcAhead + 1];
+    u4 j[kPcAhead + 1];
+    auto load = [&](int k, int ke, f4 &av, u4 &jv) {
+      const int kk = k + 4 * lane;
+      av = f4{0.f, 0.f, 0.f, 0.f};
+      jv = u4{0, 0, 0, 0};
+      if (kk < ke) {
+        av = *reinterpret_cast<const f4 *>(A.va + kk);
+        jv = *reinterpret_cast<const u4 *>(A.ci + kk);
+      }
+    };
+    auto first = [&](int g) { return __builtin_amdgcn_readfirstlane(lo[g]) & ~3; };
+#pragma unroll
+    for (int g = 0; g < kPcAhead; ++g) load(first(g), ends[g], a[g], j[g]);
+    __syncthreads();
+#pragma unroll
+    for (int g = 0; g < kPcRpl; ++g) {
+      if (r0 + (g * kPcWaves + w) * 64 >= r1) break;
+      constexpr int R = kPcAhead + 1;
+      if (g + kPcAhead < kPcRpl) load(first(g + kPcAhead), ends[g + kPcAhead], a[(g + kPcAhead) % R], j[(g + kPcAhead) % R]);
+      const int kb = first(g), ke = ends[g];
+      const int next = __shfl_down(lo[g], 1), hi = lane == 63 ? ke : next;
+      f4 av = a[g % R];
+      u4 jv = j[g % R];
+      double s = 0.0;
+      for (int k = kb;;) {
+        d2 p0, p1;
+        p0.x = (double)av.x * (double)lds.v[jv.x];
+        p0.y = (double)av.y * (double)lds.v[jv.y];
+        p1.x = (double)av.z * (double)lds.v[jv.z];
+        p1.y = (double)av.w * (double)lds.v[jv.w];
+        reinterpret_cast<d2 *>(pw)[2 * lane] = p0;
+        reinterpret_cast<d2 *>(pw)[2 * lane + 1] = p1;
+        wave_lds_order();
+        const int q1 = min(hi - k, kPcChunk);
+        for (int q = max(lo[g] - k, 0); q < q1; q += 4) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const double t = pw[q + u];
+            if (q + u < q1) s += t;
+          }
+        }
+        wave_lds_order();
+        k += kPcChunk;
+        if (k >= ke) break;
+        load(k, ke, av, jv);
+      }
+      acc[g] += s;
+    }
+  }
+}
+
+// fn(row, sum) for every row of the tile that this lane holds
+template <class F> __device__ __forceinline__ void pieces_rows(const SpPieces &A, int tile, const double (&acc)[kPcRpl],
+                                                               const F &fn) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int r0 = tile * A.tile, r1 = min(A.rows, r0 + A.tile);
+#pragma unroll
+  for (int g = 0; g < kPcRpl; ++g) {
+    const int row = r0 + (g * kPcWaves + w) * 64 + lane;
+    if (row < r1) fn(row, acc[g]);
+  }
+}
+
+struct SrcVec {
+  const float *v;
+  __device__ f4 operator()(int i) const { return *reinterpret_cast<const f4 *>(v + i); }
+};
+template <class Epi>
+__device__ __forceinline__ void pieces_rows_pass(const SpPieces &A, const float *v, const Epi &e, PcLds &lds) {
+  __shared__ double bs[kPcWaves];
+  double acc[kPcRpl], contrib = 0.0;
+  pieces_body(A, blockIdx.x, 0, A.nseg, SrcVec{v}, lds, acc);
+  pieces_rows(A, blockIdx.x, acc, [&](int row, double s) { contrib += e.row(row, s, 0.0); });
+  const double t = block_sum(contrib, bs);
+  if (threadIdx.x == 0) e.block_done(blockIdx.x, t);
+}
+
+// t = A^ x_h, r1 = d - t
+__global__ __launch_bounds__(kPcThreads) void pc_start_kernel(IterArgs<float> p) {
+  __shared__ PcLds lds;
+  EpiCgStart<float> e{{p}};
+  if (e.skip()) return;
+  pieces_rows_pass(p.pa, p.x, e, lds);
+}
+
+// q_j = A^ s_j + beta q_{j-1}
+struct EpiPcRows {
+  IterArgs<float> p;
+  double beta;
+  int has_prev;
+  __device__ double row(int i, double as, double) const {
+    const float qt = (float)(has_prev ? as + beta * (double)p.qv[i] : as);
+    p.qv[i] = qt;
+    return (double)qt * (double)qt;
+  }
+  __device__ void block_done(int b, double v) const { p.s_qq[b] = v; }
+};
+
+__global__ __launch_bounds__(kPcThreads) void pc_rows_kernel(IterArgs<float> p, int j, int cap) {
+  __shared__ PcLds lds;
+  EpiCgRows<float> e;
+  if (!cg_rows_enter<float, false>(p, j, cap, &e)) return;
+  pieces_rows_pass(p.pa, p.sv, EpiPcRows{p, e.beta, e.has_prev}, lds);
+}
+
+// alpha_j, and r1 -= alpha_j q_j.  In the pass over A^T, where every row range's
+// workgroups would do it again as they fill their segments, it cost 34 us of
+// that pass's 121; here it takes 10 and the pass finds alpha_j decided.
+__global__ __launch_bounds__(kBlock) void pc_residual_kernel(IterArgs<float> p, int j) {
+  EpiCgStep<float> e;
+  if (!cg_step_enter<float>(p, j, &e)) return;
+  for (int i = (blockIdx.x * kBlock + threadIdx.x) * 4; i < p.m; i += gridDim.x * kBlock * 4) {
+    f4 r = *reinterpret_cast<const f4 *>(p.yt + i);
+    const f4 q = *reinterpret_cast<const f4 *>(p.qv + i);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) r[u] = (float)((double)r[u] - e.alpha * (double)q[u]);
+    *reinterpret_cast<f4 *>(p.yt + i) = r;
+  }
+}
+
+// Partial sums of A^T v.  Workgroups whose index differs by a multiple of
+// `groups` (8, as the XCDs) take the same segments, so an XCD's L2 serves a
+// segment to all of them.
+template <class Src>
+__device__ __forceinline__ void pieces_cols_pass(const SpPieces &A, const Src &src, int rhs, double *part, int ncolp,
+                                                 PcLds &lds) {
+  const int grp = blockIdx.x % A.groups, tile = blockIdx.x / A.groups;
+  const int per = (A.nseg + A.groups - 1) / A.groups;
+  const int sg0 = min(A.nseg, grp * per), sg1 = min(A.nseg, sg0 + per);
+  double acc[kPcRpl];
+  pieces_body(A, tile, sg0, sg1, src, lds, acc);
+  double *o = part + (size_t)(rhs * A.groups + grp) * ncolp;
+  pieces_rows(A, tile, acc, [&](int row, double s) { o[row] = s; });
+}
+
+// A^T r1 (blockIdx.y = 0) and A^T nu_h (1)
+__global__ __launch_bounds__(kPcThreads) void pc_first_kernel(IterArgs<float> p, int ncolp) {
+  __shared__ PcLds lds;
+  if (p.ctrl->st[p.par].done) return;
+  pieces_cols_pass(p.pat, SrcVec{blockIdx.y ? p.nu : p.yt}, blockIdx.y, p.part, ncolp, lds);
+}
+
+// A^T r1 after the update of step j
+__global__ __launch_bounds__(kPcThreads) void pc_step_kernel(IterArgs<float> p, int ncolp) {
+  __shared__ PcLds lds;
+  if (p.ctrl->st[p.par].done || p.ctrl->cg.stop >= 0) return;
+  pieces_cols_pass(p.pat, SrcVec{p.yt}, 0, p.part, ncolp, lds);
+}
+
+template <class Epi>
+__device__ __forceinline__ void pieces_finish(const IterArgs<float> &p, int ncolp, int nrhs, const Epi &e) {
+  __shared__ double bs[kBlock / kWave];
+  const int col = blockIdx.x * kBlock + threadIdx.x;
+  Sum2 c{0.0, 0.0};
+  if (col < p.n) {
+    double s[2] = {0.0, 0.0};
+    for (int r = 0; r < nrhs; ++r)
+      for (int g = 0; g < p.pat.groups; ++g) s[r] += p.part[(size_t)(r * p.pat.groups + g) * ncolp + col];
+    c = e.column(col, s[0], s[1]);
+  }
+  const double a = block_sum(c.a, bs), b = block_sum(c.b, bs);
+  if (threadIdx.x == 0) e.tile_done(blockIdx.x, a, b);
+}
+
+__global__ __launch_bounds__(kBlock) void pc_first_finish_kernel(IterArgs<float> p, int ncolp) {
+  if (!cg_first_enter<float>(p)) return;
+  pieces_finish(p, ncolp, 2, EpiCgFirst<float>{p});
+}
+
+// alpha_j is stored and in r1 already (the second sum is 0).
+__global__ __launch_bounds__(kBlock) void pc_step_finish_kernel(IterArgs<float> p, int j, int ncolp) {
+  const Ctrl &q = *p.ctrl;
+  if (q.st[p.par].done || q.cg.stop >= 0) return;
+  const double beta = j > 0 ? q.cg.gamma[j & 1] / q.cg.gamma[(j - 1) & 1] : 0.0;
+  pieces_finish(p, ncolp, 1, EpiCgStep<float>{p, q.cg.alpha, beta, j > 0 ? 1 : 0, (j + 1) & 1});
+}
+
+// ---- building the pieces -----------------------------------------------------
+// Rows of the source are walked by one lane each, so a piece keeps the
+// source's order and nothing needs an atomic.
+__global__ __launch_bounds__(kBlock) void pc_count_kernel(Csr<float> A, SpPieces P) {
+  const int r = blockIdx.x * kBlock + threadIdx.x;
+  if (r >= A.rows) return;
+  for (int s = 0; s < A.nseg; ++s) {
+    const int *rp = A.rp + (size_t)s * A.rows + r;
+    for (int k = rp[0]; k < rp[1]; ++k) ++P.rp[(size_t)(A.ci[k] / P.seg) * P.rows + r];
+  }
+}
+
+__global__ __launch_bounds__(kBlock) void pc_scatter_kernel(Csr<float> A, SpPieces P, int *cur) {
+  const int r = blockIdx.x * kBlock + threadIdx.x;
+  if (r >= A.rows) return;
+  for (int s = 0; s < A.nseg; ++s) {
+    const int *rp = A.rp + (size_t)s * A.rows + r;
+    for (int k = rp[0]; k < rp[1]; ++k) {
+      const int c = A.ci[k], sg = c / P.seg, at = cur[(size_t)sg * P.rows + r]++;
+      P.va[at] = A.va[k];
+      P.ci[at] = (uint16_t)(c - sg * P.seg);
+    }
+  }
+}
+
+constexpr int kScanPer = 8, kScanBlock = kBlock * kScanPer;
+
+__global__ __launch_bounds__(kBlock) void pc_block_sums_kernel(const int *v, int64_t len, int *sums) {
+  __shared__ int red[kBlock];
+  int t = 0;
+  for (int u = 0; u < kScanPer; ++u) {
+    const int64_t i = (int64_t)blockIdx.x * kScanBlock + u * kBlock + threadIdx.x;
+    if (i < len) t += v[i];
+  }
+  red[threadIdx.x] = t;
+  for (int o = kBlock / 2; o > 0; o >>= 1) {
+    __syncthreads();
+    if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+  }
+  if (threadIdx.x == 0) sums[blockIdx.x] = red[0];
+}
+
+// Exclusive prefix sums of `mine` over the workgroup; *total: their sum.
+__device__ inline int block_prefix(int mine, int *total) {
+  __shared__ int sc[2][kBlock];
+  int b = 0;
+  sc[0][threadIdx.x] = mine;
+  __syncthreads();
+  for (int o = 1; o < kBlock; o *= 2, b ^= 1) {
+    sc[b ^ 1][threadIdx.x] = sc[b][threadIdx.x] + ((int)threadIdx.x >= o ? sc[b][threadIdx.x - o] : 0);
+    __syncthreads();
+  }
+  const int incl = sc[b][threadIdx.x];
+  *total = sc[b][kBlock - 1];
+  __syncthreads();
+  return incl - mine;
+}
+
+__global__ __launch_bounds__(kBlock) void pc_scan_sums_kernel(int *sums, int64_t len) {
+  int carry = 0;
+  for (int64_t i0 = 0; i0 < len; i0 += kBlock) {
+    const int64_t i = i0 + threadIdx.x;
+    int total;
+    const int at = block_prefix(i < len ? sums[i] : 0, &total);
+    if (i < len) sums[i] = carry + at;
+    carry += total;
+  }
+}
+
+__global__ __launch_bounds__(kBlock) void pc_scan_kernel(int *v, int *copy, int64_t len, const int *sums, int nnz) {
+  const int64_t i0 = (int64_t)blockIdx.x * kScanBlock + (int64_t)threadIdx.x * kScanPer;
+  int x[kScanPer], t = 0, total;
+  for (int u = 0; u < kScanPer; ++u) {
+    x[u] = i0 + u < len ? v[i0 + u] : 0;
+    t += x[u];
+  }
+  int at = sums[blockIdx.x] + block_prefix(t, &total);
+  for (int u = 0; u < kScanPer; ++u)
+    if (i0 + u < len) {
+      v[i0 + u] = copy[i0 + u] = at;
+      at += x[u];
+    }
+  if (blockIdx.x == 0 && threadIdx.x == 0) v[len] = nnz;
+}
+
+__global__ __launch_bounds__(kPcPad) void pc_pad_kernel(SpPieces P, int64_t nnz) {
+  P.va[nnz + threadIdx.x] = 0.f;
+  P.ci[nnz + threadIdx.x] = 0;
+}
+__global__ __launch_bounds__(kBlock) void pc_zero_kernel(int *v, int64_t len) {
+  for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < len; i += (int64_t)gridDim.x * kBlock) v[i] = 0;
+}
+
+}  // namespace
+
+// Where the pieces are faster (CG step of the plain passes -> in pieces, us):
+//  - at least a million entries, so that the pass is bound by them:
+//    200000 x 50000, 6 a row: 31.6 -> 29.1; 2000000 x 200000, 16 a row: 500 -> 188;
+//  - at least 6 of a workgroup's 16 waves with rows of their own:
+//    100000 x 25000, 10 a row (7 and 12 waves): 31.1 -> 26.5;
+//    100000 x 10000, 20 a row (7 and 5): 40.7 -> 41.6;
+//  - at least one entry per row and segment, or the row bounds outweigh them:
+//    500000 x 125000, 9 a row (2.3): 84.7 -> 49.7;
+//    1000000 x 250000, 6 a row (0.75): 95.7 -> 94.9 and the first pass 103 -> 125.
+bool pieces_shape(int64_t rows, int64_t cols, int64_t nnz, int groups, SpPieces *P) {
+  *P = SpPieces{};
+  int64_t nseg = round_up(cdiv(cols, (int64_t)kPcSeg), groups);
+  const int64_t seg = round_up(cdiv(cols, nseg), 64);
+  nseg = cdiv(cols, seg);
+  const int64_t wgs = kPcWg / groups, rounds = cdiv(rows, wgs * kPcTile);
+  if (nnz < ((int64_t)1 << 20) || rows < wgs * 64 * 6 || nnz < rows * nseg) return false;
+  if (rows * nseg >= (1LL << 31) - 1 || nnz >= (1LL << 31) - kPcPad - 1) return false;
+  P->rows = (int)rows;
+  P->cols = (int)cols;
+  P->seg = (int)seg;
+  P->nseg = (int)nseg;
+  P->tile = (int)round_up(cdiv(rows, wgs * rounds), 64);
+  P->tiles = (int)cdiv(rows, (int64_t)P->tile);
+  P->groups = groups;
+  return true;
+}
+
+int64_t pieces_sums(const SpPieces &P) { return cdiv((int64_t)P.rows * P.nseg, (int64_t)kScanBlock); }
+
+void fill_pieces(const Csr<float> &A, const SpPieces &P, int64_t nnz, int *cur, int *sums, hipStream_t s) {
+  const int64_t len = (int64_t)P.rows * P.nseg, blocks = pieces_sums(P);
+  const dim3 rows(cdiv(A.rows, kBlock)), b(kBlock);
+  hipLaunchKernelGGL(pc_zero_kernel, dim3(1024), b, 0, s, P.rp, len + 1);
+  hipLaunchKernelGGL(pc_count_kernel, rows, b, 0, s, A, P);
+  hipLaunchKernelGGL(pc_block_sums_kernel, dim3(blocks), b, 0, s, (const int *)P.rp, len, sums);
+  hipLaunchKernelGGL(pc_scan_sums_kernel, dim3(1), b, 0, s, sums, blocks);
+  hipLaunchKernelGGL(pc_scan_kernel, dim3(blocks), b, 0, s, P.rp, cur, len, (const int *)sums, (int)nnz);
+  hipLaunchKernelGGL(pc_scatter_kernel, rows, b, 0, s, A, P, cur);
+  hipLaunchKernelGGL(pc_pad_kernel, dim3(1), dim3(kPcPad), 0, s, P, nnz);
+}
+
+int pieces_finish_blocks(int n) { return (int)cdiv(n, kBlock); }
+
+void launch_pc_first(const IterArgs<float> &p, int ncolp, hipStream_t s) {
+  hipLaunchKernelGGL(pc_start_kernel, dim3(p.pa.tiles), dim3(kPcThreads), 0, s, p);
+  hipLaunchKernelGGL(pc_first_kernel, dim3(p.pat.tiles * p.pat.groups, 2), dim3(kPcThreads), 0, s, p, ncolp);
+  hipLaunchKernelGGL(pc_first_finish_kernel, dim3(pieces_finish_blocks(p.n)), dim3(kBlock), 0, s, p, ncolp);
+}
+
+void launch_pc_rows(const IterArgs<float> &p, int j, int cap, hipStream_t s) {
+  hipLaunchKernelGGL(pc_rows_kernel, dim3(p.pa.tiles), dim3(kPcThreads), 0, s, p, j, cap);
+}
+
+void launch_pc_step(const IterArgs<float> &p, int j, int cap, int ncolp, hipStream_t s) {
+  launch_pc_rows(p, j, cap, s);
+  hipLaunchKernelGGL(pc_residual_kernel, dim3(std::min<int64_t>(512, cdiv(p.m, 4 * kBlock))), dim3(kBlock), 0, s, p, j);
+  hipLaunchKernelGGL(pc_step_kernel, dim3(p.pat.tiles * p.pat.groups), dim3(kPcThreads), 0, s, p, ncolp);
+  hipLaunchKernelGGL(pc_step_finish_kernel, dim3(pieces_finish_blocks(p.n)), dim3(kBlock), 0, s, p, j, ncolp);
+}
+
+}  // namespace pogs

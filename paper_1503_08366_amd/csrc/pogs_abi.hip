@@ -185,9 +185,10 @@ template <typename T> int alloc_iteration(pogs_ctx *c) {
   gemv_t_geometry(m, n, sizeof(T), &c->splits, &c->rps, &c->ncolp);
   c->nbx = (int)cdiv(n, kBlock);
   c->nby = (int)cdiv(m, kBlock);
-  c->n_pri = c->sparse ? c->sp_grid : gemv_n_blocks(m, n, sizeof(T), 0);
-  c->n_dual = c->sparse ? c->sp_gridt : (int)cdiv(n, kFinishCols);
-  if (c->sparse) c->splits = 1;  // no column-sum partials
+  const bool pieces = c->sp_pa.rp != nullptr;
+  c->n_pri = pieces ? c->sp_pa.tiles : c->sparse ? c->sp_grid : gemv_n_blocks(m, n, sizeof(T), 0);
+  c->n_dual = pieces ? pieces_finish_blocks(n) : c->sparse ? c->sp_gridt : (int)cdiv(n, kFinishCols);
+  if (c->sparse) c->splits = pieces ? c->sp_pat.groups : 1;  // partials of the column sums
   // prox sums (two parities), residual sums, CGLS sums (||s||^2 and s^T p by
   // step parity, ||q||^2), then the unscale kernel's sums
   c->fp_blocks = one_pass_blocks(m, n, c->ld, (int)sizeof(T), c->sparse);
@@ -451,6 +452,37 @@ void transpose_csr(const HostCsr &a, int n, int seg, HostCsr *t) {
   }
 }
 
+void drop_pieces(pogs_ctx *c, SpPieces *p) {
+  c->arena.release(p->rp);
+  c->arena.release(p->ci);
+  c->arena.release(p->va);
+  *p = SpPieces{};
+}
+
+// The copies in pieces where the shapes ask for them (a segment length given
+// by the caller is kept) and the memory is there.
+int init_pieces(pogs_ctx *c, const Csr<float> &a, const Csr<float> &at, int64_t nnz) {
+  SpPieces P[2];
+  if (!pieces_shape(c->m, c->n, nnz, 1, &P[0]) || !pieces_shape(c->n, c->m, nnz, 8, &P[1])) return POGS_OK;
+  DevArena tmp(c->stream);
+  int *cur[2], *sums[2];
+  for (int k = 0; k < 2; ++k) {
+    const size_t len = (size_t)P[k].rows * P[k].nseg;
+    if (c->arena.alloc((void **)&P[k].rp, (len + 1) * 4) ||
+        c->arena.alloc((void **)&P[k].ci, ((size_t)nnz + kPcPad) * 2) ||
+        c->arena.alloc((void **)&P[k].va, ((size_t)nnz + kPcPad) * 4) || tmp.alloc((void **)&cur[k], len * 4) ||
+        tmp.alloc((void **)&sums[k], (size_t)pieces_sums(P[k]) * 4)) {
+      for (SpPieces &q : P) drop_pieces(c, &q);
+      return POGS_OK;
+    }
+  }
+  fill_pieces(a, P[0], nnz, cur[0], sums[0], c->stream);
+  fill_pieces(at, P[1], nnz, cur[1], sums[1], c->stream);
+  c->sp_pa = P[0];
+  c->sp_pat = P[1];
+  return POGS_OK;
+}
+
 template <typename T> int init_sparse_impl(pogs_ctx *c, const HostCsr &a, const HostCsr &t) {
   const int m = (int)c->m, n = (int)c->n;
   const size_t nnz = a.ci.size();
@@ -483,6 +515,9 @@ template <typename T> int init_sparse_impl(pogs_ctx *c, const HostCsr &a, const 
   const double eps = c->params.eps_cmp > 0.0 ? c->params.eps_cmp : (sizeof(T) == 4 ? (double)FLT_EPSILON : DBL_EPSILON);
   const IterArgs<T> ia = c->iter_args<T>();
   run_equilibrate_sparse<T>(ia.sa, ia.sat, m, n, c->params.equil_iters, eps, c->D, c->E, ws, s);
+  if constexpr (sizeof(T) == 4) {
+    if (c->params.sparse_segment == 0 && (rc = init_pieces(c, ia.sa, ia.sat, (int64_t)nnz))) return rc;
+  }
   POGS_HIP_TRY(hipStreamSynchronize(s));  // the host copies above are pageable
   POGS_HIP_TRY(hipGetLastError());
   return POGS_OK;
@@ -533,6 +568,11 @@ extern "C" int pogs_init_sparse(pogs_ctx **out, int64_t m, int64_t n, int64_t nn
   c->arena.stream = c->stream;
   rc = dt == POGS_F32 ? init_sparse_impl<float>(c, a, t) : init_sparse_impl<double>(c, a, t);
   if (!rc) rc = dt == POGS_F32 ? alloc_iteration<float>(c) : alloc_iteration<double>(c);
+  if (rc == POGS_ENOMEM && c->sp_pa.rp) {  // without them it may fit
+    drop_pieces(c, &c->sp_pa);
+    drop_pieces(c, &c->sp_pat);
+    rc = alloc_iteration<float>(c);
+  }
   if (!rc && hipStreamSynchronize(c->stream) != hipSuccess) rc = POGS_EDEVICE;
   if (rc) {
     delete c;
@@ -606,7 +646,7 @@ void launch_iters(pogs_ctx *c, int i0, int i1, bool preview, int cg_cap, int gap
   for (int i = i0; i < i1; ++i) {
     p = (i & 1) ? p1 : p0;  // half-step set by iteration parity (one-pass iteration)
     p.par = i & 1;
-    if (c->sparse) launch_iteration_cg_sparse<T>(p, cg_cap, s);
+    if (c->sparse) launch_iteration_cg_sparse<T>(p, cg_cap, c->ncolp, s);
     else if (cg_cap > 0) launch_iteration_cg<T>(p, c->splits, c->rps, c->ncolp, cg_cap, s);
     else if (gap) launch_iteration_gap<T>(p, c->splits, c->rps, c->ncolp, s);
     else launch_iteration<T>(p, c->splits, c->rps, c->ncolp, s);
@@ -925,7 +965,7 @@ template <typename T> int profile_impl(pogs_ctx *c, int reps, double *ms) {
   }
   ms[0] = (double)t / ((double)launches * chunk);
   auto part = [&](int w) {
-    if (c->sparse) launch_iteration_cg_sparse_part<T>(p, w, s);
+    if (c->sparse) launch_iteration_cg_sparse_part<T>(p, w, c->ncolp, s);
     else if (cg_cap > 0) launch_iteration_cg_part<T>(p, w, c->splits, c->rps, c->ncolp, s);
     else launch_iteration_part<T>(p, w, c->splits, c->rps, c->ncolp, s);
   };

@@ -3,7 +3,10 @@
 // so both products of a CG step are row passes with no cross-workgroup
 // reduction: A^ p is a pass over the rows of A^, A^T [r1, q] one over the
 // rows of A^T, and each finishes in its own epilogue.  A CG step is two
-// launches (the dense path needs three).
+// launches (the dense path needs three).  Large float32 matrices run the same
+// iteration over a copy in pieces (pieces.hip); the passes here remain for the
+// pre-conditioning and the warm start, for float64, for smaller matrices and
+// where the caller gives the segment length.
 //
 // Row pass: a group of lpr lanes per row (lpr chosen from the mean row length)
 // walks the row's entries with stride lpr, accumulates in float64 and
@@ -340,14 +343,27 @@ template <typename T> static void launch_sp_step(const IterArgs<T> &p, int j, in
   POGS_SP_DISPATCH(p.sat.lpr, sp_step_kernel, p.sat.grid, s, p, j)
 }
 
-template <typename T> void launch_iteration_cg_sparse(const IterArgs<T> &p, int cap, hipStream_t s) {
+template <typename T> void launch_iteration_cg_sparse(const IterArgs<T> &p, int cap, int ncolp, hipStream_t s) {
   launch_prox_cg<T>(p, s);
+  if constexpr (sizeof(T) == 4) {
+    if (p.pa.rp) {
+      launch_pc_first(p, ncolp, s);
+      for (int j = 0; j < cap; ++j) launch_pc_step(p, j, cap, ncolp, s);
+      launch_pc_rows(p, cap, cap, s);
+      return;
+    }
+  }
   launch_sp_first<T>(p, s);
   for (int j = 0; j < cap; ++j) launch_sp_step<T>(p, j, cap, s);
   launch_sp_rows<T>(p, cap, cap, s);
 }
 
-template <typename T> void launch_iteration_cg_sparse_part(const IterArgs<T> &p, int which, hipStream_t s) {
+template <typename T>
+void launch_iteration_cg_sparse_part(const IterArgs<T> &p, int which, int ncolp, hipStream_t s) {
+  if constexpr (sizeof(T) == 4) {
+    if (p.pa.rp && which == 1) return launch_pc_first(p, ncolp, s);
+    if (p.pa.rp && which > 1) return launch_pc_step(p, 0, 1 << 30, ncolp, s);
+  }
   if (which == 0) launch_prox_cg<T>(p, s);
   else if (which == 1) launch_sp_first<T>(p, s);
   else launch_sp_step<T>(p, 0, 1 << 30, s);
@@ -405,8 +421,8 @@ void launch_warm_start_sparse(const IterArgs<T> &p, const double *D, const doubl
 #define POGS_INST(T)                                                                                        \
   template void run_equilibrate_sparse<T>(Csr<T>, Csr<T>, int, int, int, double, double *, double *,        \
                                           double *, hipStream_t);                                           \
-  template void launch_iteration_cg_sparse<T>(const IterArgs<T> &, int, hipStream_t);                       \
-  template void launch_iteration_cg_sparse_part<T>(const IterArgs<T> &, int, hipStream_t);                  \
+  template void launch_iteration_cg_sparse<T>(const IterArgs<T> &, int, int, hipStream_t);                    \
+  template void launch_iteration_cg_sparse_part<T>(const IterArgs<T> &, int, int, hipStream_t);                \
   template void launch_warm_start_sparse<T>(const IterArgs<T> &, const double *, const double *, double,      \
                                             const T *, const T *, hipStream_t);
 POGS_INST(float)
