@@ -473,7 +473,7 @@ template <typename T> static void launch_step(const IterArgs<T> &p, int j, int c
 
 template <typename T>
 void launch_iteration_cg(const IterArgs<T> &p, int splits, int rps, int ncolp, int cap, hipStream_t s) {
-  hipLaunchKernelGGL(prox_cg_kernel<T>, dim3(p.nbx + p.nby), dim3(kBlock), 0, s, p);
+  hipLaunchKernelGGL(prox_cg_kernel<T>, dim3(p.n_smu + p.n_syh), dim3(kBlock), 0, s, p);
   launch_first<T>(p, splits, rps, ncolp, s);
   for (int j = 0; j < cap; ++j) launch_step<T>(p, j, cap, splits, rps, ncolp, s);
   if constexpr (sizeof(T) == 4) {
@@ -484,13 +484,13 @@ void launch_iteration_cg(const IterArgs<T> &p, int splits, int rps, int ncolp, i
 
 template <typename T>
 void launch_iteration_cg_part(const IterArgs<T> &p, int which, int splits, int rps, int ncolp, hipStream_t s) {
-  if (which == 0) hipLaunchKernelGGL(prox_cg_kernel<T>, dim3(p.nbx + p.nby), dim3(kBlock), 0, s, p);
+  if (which == 0) hipLaunchKernelGGL(prox_cg_kernel<T>, dim3(p.n_smu + p.n_syh), dim3(kBlock), 0, s, p);
   else if (which == 1) launch_first<T>(p, splits, rps, ncolp, s);
   else launch_step<T>(p, 0, 1 << 30, splits, rps, ncolp, s);
 }
 
 template <typename T> void launch_prox_cg(const IterArgs<T> &p, hipStream_t s) {
-  hipLaunchKernelGGL(prox_cg_kernel<T>, dim3(p.nbx + p.nby), dim3(kBlock), 0, s, p);
+  hipLaunchKernelGGL(prox_cg_kernel<T>, dim3(p.n_smu + p.n_syh), dim3(kBlock), 0, s, p);
 }
 
 template <typename T> void launch_cg_from_state(const IterArgs<T> &p, hipStream_t s) {

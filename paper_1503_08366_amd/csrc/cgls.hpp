@@ -22,9 +22,73 @@ __device__ inline double block_total(const double *slots, int len, double *scrat
   return scratch[0];
 }
 
+// The prox step (prox_body's arithmetic and its stop test).  The state is read
+// as the CGLS projection leaves it: x~ = c - x, y = d - r1, y~ = r1 (r1 kept in
+// yt), and x is set to the half step x_h, where the next projection starts.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void prox_cg_kernel(IterArgs<T> p) {
-  prox_body<T, true>(hw_block(), p);
+  __shared__ double bs[4 * (kBlock / kWave)];
+  __shared__ CtrlState st;
+  const int par = p.par;
+  const bool xs = (int)blockIdx.x < p.n_smu;
+  const int blk = xs ? blockIdx.x : blockIdx.x - p.n_smu;
+  const unsigned len = xs ? p.n : p.m, stride = (xs ? p.n_smu : p.n_syh) * kBlock;  // i passes len by up to a stride
+  const FnDev<T> &F = xs ? p.g : p.f;
+  unsigned i = (unsigned)blk * kBlock + threadIdx.x;
+  T vi = T(0), vti = T(0), fa = T(0), fb = T(0), fc = T(0), fd = T(0), fe = T(0);
+  int fh = 0;
+  auto load = [&]() {
+    if (i >= len) return;
+    if (xs) {
+      vi = p.x[i];
+      vti = p.cx[i] - vi;
+    } else {
+      vti = p.yt[i];
+      vi = p.dy[i] - vti;
+    }
+    fh = F.h[i];
+    fa = F.a[i];
+    fb = F.b[i];
+    fc = F.c[i];
+    fd = F.d[i];
+    fe = F.e[i];
+  };
+  // every load that does not depend on the control state goes out first
+  if (threadIdx.x == 0) st = p.ctrl->st[1 - par];
+  double part[4];
+  control_partials(p, 1 - par, part);
+  load();
+  __syncthreads();
+  if (!st.done && st.pending) control_apply(p, part, st, bs);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    CtrlState out = st;
+    out.pending = st.done ? 0 : 1;
+    p.ctrl->st[par] = out;
+  }
+  if (st.done) return;
+  const T rho = (T)st.rho, resc = (T)st.rescale, alpha = (T)p.ctrl->alpha;
+  double contrib = 0.0;
+  while (i < len) {
+    const HalfStep<T> hs = half_step<T>(fh, fa, fb, fc, fd, fe, vi, vti, rho, resc, alpha);
+    if (xs) {
+      p.xh[i] = hs.h;
+      p.mu[i] = hs.dual;
+      p.cx[i] = hs.proj_in;
+      p.x[i] = hs.h;
+    } else {
+      p.yh[i] = hs.h;
+      p.nu[i] = hs.dual;
+      p.dy[i] = hs.proj_in;
+    }
+    contrib += xs ? (double)hs.dual * (double)hs.dual : (double)hs.h * (double)hs.h;
+    i += stride;
+    load();
+  }
+  const double s = block_sum(contrib, bs);
+  if (threadIdx.x == 0) {
+    if (xs) p.s_mu[(size_t)par * p.n_smu + blk] = s;
+    else p.s_yh[(size_t)par * p.n_syh + blk] = s;
+  }
 }
 
 // C0: t = A^ x_h -> r1 = d - t (kept in yt), (t - y_h)^2 per row

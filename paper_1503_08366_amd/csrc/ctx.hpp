@@ -354,8 +354,8 @@ struct pogs_ctx {
     p.nbx = nbx;
     p.nby = nby;
     p.fused = fused ? 1 : 0;
-    p.n_smu = fused ? n_dual : nbx;
-    p.n_syh = fused ? std::max(splits, fp_blocks) : nby;
+    p.n_smu = fused ? n_dual : sparse ? capped_blocks(nbx) : nbx;
+    p.n_syh = fused ? std::max(splits, fp_blocks) : sparse ? capped_blocks(nby) : nby;
     p.s_mu = slots;                    // 2 x n_smu (by iteration parity), room for 2 x smu_cap
     p.s_yh = slots + 2 * smu_cap;      // 2 x n_syh, room for 2 x syh_cap
     p.s_pri = p.s_yh + 2 * syh_cap;    // n_pri, room for pri_cap()

@@ -174,7 +174,7 @@ __device__ __forceinline__ IterArgs<float> iter_args(const GProb &P, int par) {
 
 __global__ __launch_bounds__(kBlock) void g_prox(const GProb *probs, const GItem *items, int par) {
   GROUP_ITEM();
-  prox_body<float, false, true>(b, iter_args(P, par));
+  prox_body<float, true>(b, iter_args(P, par));
 }
 
 // The solve's epilogue for either orientation (chosen per problem).

@@ -556,7 +556,7 @@ int GroupEngine::finish(const std::vector<int> &handles) {
   std::vector<std::vector<GItem>> lists(1);
   for (int h : handles) {
     const GProb &P = probs_[h];
-    push_range(lists[0], h, P.it.nbx + P.it.nby);
+    push_range(lists[0], h, capped_blocks(P.it.nbx) + capped_blocks(P.it.nby));
   }
   std::vector<const GItem *> ptr;
   int rc;

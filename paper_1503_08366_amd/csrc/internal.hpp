@@ -86,6 +86,15 @@ constexpr size_t kSegBytes = (size_t)1 << 20;
 constexpr int kSegRows = 512;
 constexpr int kSegGrid = 2048;
 
+// Workgroups of an elementwise launch over `blocks` blocks of elements whose
+// workgroups each do something that grows with their number: the CGLS prox step
+// (every workgroup sums the partials of all of them for the stop test) and the
+// unscale step (they arrive at one counter, 120 ns each).  2200000 elements on
+// gfx950: prox 75 -> 25 us, unscale 1060 -> 240 us; up to 262144 elements a side
+// nothing changes.
+constexpr int kCappedBlocks = 1024;
+__host__ __device__ inline int capped_blocks(int blocks) { return blocks < kCappedBlocks ? blocks : kCappedBlocks; }
+
 // A sparse float32 matrix split by columns into nseg segments of seg columns,
 // as many as fit in a workgroup's LDS (pieces.hip): the entries of row r in
 // segment s are [rp[s rows + r], rp[s rows + r + 1]) of va and of ci, ci the

@@ -363,7 +363,7 @@ void launch_unscale(const IterArgs<T> &p, const double *D, const double *E, cons
                     const double *gc0, const double *gd0, const double *ge0, T *xo, T *yo, T *muo,
                     T *nuo, double *obj_slots, double *obj_out, unsigned *cnt, int from_state, double rho,
                     hipStream_t s) {
-  hipLaunchKernelGGL(unscale_kernel<T>, dim3(p.nbx + p.nby), dim3(kBlock), 0, s, p, D, E, fh0, fa0, fb0,
+  hipLaunchKernelGGL(unscale_kernel<T>, dim3(capped_blocks(p.nbx) + capped_blocks(p.nby)), dim3(kBlock), 0, s, p, D, E, fh0, fa0, fb0,
                      fc0, fd0, fe0, gh0, ga0, gb0, gc0, gd0, ge0, xo, yo, muo, nuo, obj_slots, obj_out, cnt,
                      from_state, rho);
 }

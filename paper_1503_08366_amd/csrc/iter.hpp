@@ -161,10 +161,8 @@ __device__ __forceinline__ HalfStep<T> half_step(int fh, T fa, T fb, T fc, T fd,
 // ---------------------------------------------------------------------------
 // 1. prox step (runs the previous iteration's stop test first)
 // ---------------------------------------------------------------------------
-// With CG (the CGLS projection) the state is read as that projection leaves
-// it: x~ = c - x, y = d - r1, y~ = r1 (r1 kept in yt), and x is set to the
-// half step x_h, where the next projection starts.  GROUPED: see prox_logistic.
-template <typename T, bool CG = false, bool GROUPED = false>
+// GROUPED: see prox_logistic.
+template <typename T, bool GROUPED = false>
 __device__ __forceinline__ void prox_body(const Blk &b, const IterArgs<T> &p) {
   __shared__ double bs[4 * (kBlock / kWave)];
   __shared__ CtrlState st;
@@ -183,18 +181,8 @@ __device__ __forceinline__ void prox_body(const Blk &b, const IterArgs<T> &p) {
   T vi = T(0), vti = T(0), fa = T(0), fb = T(0), fc = T(0), fd = T(0), fe = T(0);
   int fh = 0;
   if (i < len) {
-    if constexpr (CG) {
-      if (xs) {
-        vi = p.x[i];
-        vti = p.cx[i] - vi;
-      } else {
-        vti = p.yt[i];
-        vi = p.dy[i] - vti;
-      }
-    } else {
-      vi = v[i];
-      vti = vt[i];
-    }
+    vi = v[i];
+    vti = vt[i];
     fh = F.h[i];
     fa = F.a[i];
     fb = F.b[i];
@@ -213,13 +201,11 @@ __device__ __forceinline__ void prox_body(const Blk &b, const IterArgs<T> &p) {
   const T rho = (T)st.rho;
   const T resc = (T)st.rescale;
   const T alpha = (T)p.ctrl->alpha;
-  const bool gap = !CG && p.ctrl->stop_gap;
+  const bool gap = p.ctrl->stop_gap;
   double contrib = 0.0, gobj = 0.0, gconj = 0.0;
   if (i < len) {
     const HalfStep<T> hs = half_step<T, GROUPED>(fh, fa, fb, fc, fd, fe, vi, vti, rho, resc, alpha);
-    if constexpr (!CG) {
-      if (resc != T(1)) vt[i] = hs.vt;
-    }
+    if (resc != T(1)) vt[i] = hs.vt;
     if (gap) {
       // the state is primal and dual feasible: value at (x, y), conjugate at
       // (mu, nu) = (-rho x~, -rho y~)
@@ -231,7 +217,6 @@ __device__ __forceinline__ void prox_body(const Blk &b, const IterArgs<T> &p) {
       p.xh[i] = h;
       p.mu[i] = dual;
       p.cx[i] = hs.proj_in;
-      if constexpr (CG) p.x[i] = h;
     } else {
       p.yh[i] = h;
       p.nu[i] = dual;
@@ -927,24 +912,26 @@ __device__ __forceinline__ void unscale_body(
     T *yo, T *muo, T *nuo, double *slots, double *obj, unsigned *cnt, int from_state = 0, double rho = 0.0) {
   __shared__ double bs[kBlock / kWave];
   __shared__ int flag;
-  const bool xs = b.x < p.nbx;
-  const int blk = xs ? b.x : b.x - p.nbx;
-  const int i = blk * kBlock + threadIdx.x;
+  const int nbx = capped_blocks(p.nbx), nby = capped_blocks(p.nby);
   double contrib = 0.0;
-  if (xs && i < p.n) {
-    const double xv = from_state ? (double)p.x[i] : (double)p.xh[i];
-    const double mv = from_state ? -rho * (double)p.xt[i] : (double)p.mu[i];
-    const double x = E[i] * xv;
-    if (xo) xo[i] = (T)x;
-    if (muo) muo[i] = (T)(mv / E[i]);
-    contrib = fn_value(gh[i], ga[i], gb[i], gc[i], gd[i], ge[i], x);
-  } else if (!xs && i < p.m) {
-    const double yv = from_state ? (double)p.y[i] : (double)p.yh[i];
-    const double nv = from_state ? -rho * (double)p.yt[i] : (double)p.nu[i];
-    const double y = yv / D[i];
-    if (yo) yo[i] = (T)y;
-    if (nuo) nuo[i] = (T)(D[i] * nv);
-    contrib = fn_value(fh[i], fa[i], fb[i], fc[i], fd[i], fe[i], y);
+  if (b.x < nbx) {
+    for (unsigned i = (unsigned)b.x * kBlock + threadIdx.x; i < (unsigned)p.n; i += nbx * kBlock) {
+      const double xv = from_state ? (double)p.x[i] : (double)p.xh[i];
+      const double mv = from_state ? -rho * (double)p.xt[i] : (double)p.mu[i];
+      const double x = E[i] * xv;
+      if (xo) xo[i] = (T)x;
+      if (muo) muo[i] = (T)(mv / E[i]);
+      contrib += fn_value(gh[i], ga[i], gb[i], gc[i], gd[i], ge[i], x);
+    }
+  } else {
+    for (unsigned i = (unsigned)(b.x - nbx) * kBlock + threadIdx.x; i < (unsigned)p.m; i += nby * kBlock) {
+      const double yv = from_state ? (double)p.y[i] : (double)p.yh[i];
+      const double nv = from_state ? -rho * (double)p.yt[i] : (double)p.nu[i];
+      const double y = yv / D[i];
+      if (yo) yo[i] = (T)y;
+      if (nuo) nuo[i] = (T)(D[i] * nv);
+      contrib += fn_value(fh[i], fa[i], fb[i], fc[i], fd[i], fe[i], y);
+    }
   }
   const double s = block_sum(contrib, bs);
   if (threadIdx.x == 0) slots[b.x] = s;

@@ -375,7 +375,7 @@ bool pieces_shape(int64_t rows, int64_t cols, int64_t nnz, int groups, SpPieces 
   nseg = cdiv(cols, seg);
   const int64_t wgs = kPcWg / groups, rounds = cdiv(rows, wgs * kPcTile);
   if (nnz < ((int64_t)1 << 20) || rows < wgs * 64 * 6 || nnz < rows * nseg) return false;
-  if (rows * nseg >= (1LL << 31) - 1 || nnz >= (1LL << 31) - kPcPad - 1) return false;
+  if (rows >= (1LL << 30) || cols >= (1LL << 30) || rows * nseg >= (1LL << 31) - 1 || nnz >= (1LL << 31) - kPcPad - 1) return false;
   P->rows = (int)rows;
   P->cols = (int)cols;
   P->seg = (int)seg;
