@@ -202,7 +202,7 @@ class HostUploader {
 // A pool for other host-side copies (the serving engine's private copy of
 // each request), separate from the uploader's so the two run side by side.
 inline CopyPool &host_pool() {
-  static CopyPool *p = new CopyPool(3);
+  static CopyPool *p = new CopyPool(7);
   return *p;
 }
 
