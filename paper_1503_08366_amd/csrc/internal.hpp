@@ -220,10 +220,10 @@ int run_factor_inverse(double *K, int q, int Q, T *Kinv, int ldk, double *ws, un
 size_t factor_workspace_bytes(int Q);
 
 // ---- launchers (iter.hip) -------------------------------------------------
-template <typename T> void launch_scale_fn(const uint8_t *h, const double *a, const double *b,
-                                           const double *c, const double *d, const double *e,
-                                           const double *scale, bool divide, int len, uint8_t *oh,
-                                           T *oa, T *ob, T *oc, T *od, T *oe, hipStream_t s);
+template <typename T>
+void launch_scale_fns(const uint8_t *fh, const double *f, const double *D, int m, uint8_t *ofh, T *of,
+                      const uint8_t *gh, const double *g, const double *E, int n, uint8_t *ogh, T *og, hipStream_t s);
+template <typename T> void launch_start_state(T *vec, size_t elems, Ctrl *ctrl, const Ctrl &h, hipStream_t s);
 template <typename T> void launch_iteration(const IterArgs<T> &p, int splits, int rows_per_split,
                                             int ncolp, hipStream_t s);
 // The same iteration with the gap test between the prox step and pass 1.

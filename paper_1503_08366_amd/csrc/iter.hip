@@ -330,20 +330,43 @@ void launch_warm_start(const IterArgs<T> &p, int splits, int rps, int ncolp, con
   }
 }
 
+// f^(y) = f(y / D) (blockIdx.y = 0) and g^(x) = g(E x) (1); raw parameters and
+// scaled ones as five arrays one after the other.
 template <typename T>
-__global__ __launch_bounds__(kBlock) void scale_fn_kernel(const uint8_t *h, const double *a, const double *b,
-                                                          const double *c, const double *d, const double *e,
-                                                          const double *scale, bool divide, int len, uint8_t *oh,
-                                                          T *oa, T *ob, T *oc, T *od, T *oe) {
-  scale_fn_body<T>(hw_block(), h, a, b, c, d, e, scale, divide, len, oh, oa, ob, oc, od, oe);
+__global__ __launch_bounds__(kBlock) void scale_fns_kernel(const uint8_t *fh, const double *f, const double *D, int m,
+                                                           uint8_t *ofh, T *of, const uint8_t *gh, const double *g,
+                                                           const double *E, int n, uint8_t *ogh, T *og) {
+  const bool fs = blockIdx.y == 0;
+  const size_t len = fs ? m : n;
+  const double *v = fs ? f : g;
+  T *o = fs ? of : og;
+  const Blk b{(int)blockIdx.x, 0, (int)gridDim.x, 1};
+  scale_fn_body<T>(b, fs ? fh : gh, v, v + len, v + 2 * len, v + 3 * len, v + 4 * len, fs ? D : E, fs, (int)len,
+                   fs ? ofh : ogh, o, o + len, o + 2 * len, o + 3 * len, o + 4 * len);
 }
 
 template <typename T>
-void launch_scale_fn(const uint8_t *h, const double *a, const double *b, const double *c, const double *d,
-                     const double *e, const double *scale, bool divide, int len, uint8_t *oh, T *oa,
-                     T *ob, T *oc, T *od, T *oe, hipStream_t s) {
-  hipLaunchKernelGGL(scale_fn_kernel<T>, dim3(cdiv(len, kBlock)), dim3(kBlock), 0, s, h, a, b, c, d, e,
-                     scale, divide, len, oh, oa, ob, oc, od, oe);
+void launch_scale_fns(const uint8_t *fh, const double *f, const double *D, int m, uint8_t *ofh, T *of,
+                      const uint8_t *gh, const double *g, const double *E, int n, uint8_t *ogh, T *og, hipStream_t s) {
+  hipLaunchKernelGGL(scale_fns_kernel<T>, dim3(cdiv(std::max(m, n), kBlock), 2), dim3(kBlock), 0, s, fh, f, D, m, ofh,
+                     of, gh, g, E, n, ogh, og);
+}
+
+// The state a solve starts from: every vector zero and the control block h.
+template <typename T>
+__global__ __launch_bounds__(kBlock) void start_state_kernel(T *vec, size_t elems, Ctrl *ctrl, Ctrl h) {
+  typedef T V __attribute__((ext_vector_type(16 / sizeof(T))));  // elems is a multiple of 64
+  const V zero = {};
+  const size_t pieces = elems / (16 / sizeof(T));
+  for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < pieces; i += (size_t)gridDim.x * kBlock)
+    reinterpret_cast<V *>(vec)[i] = zero;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *ctrl = h;
+}
+
+template <typename T> void launch_start_state(T *vec, size_t elems, Ctrl *ctrl, const Ctrl &h, hipStream_t s) {
+  const size_t pieces = elems / (16 / sizeof(T));
+  hipLaunchKernelGGL(start_state_kernel<T>, dim3(std::min<size_t>(2048, (pieces + kBlock - 1) / kBlock)), dim3(kBlock), 0,
+                     s, vec, elems, ctrl, h);
 }
 
 template <typename T>
@@ -403,9 +426,10 @@ void launch_prox_eval(const uint8_t *h, const T *a, const T *b, const T *c, cons
                                   hipStream_t);                                                        \
   template void launch_warm_start<T>(const IterArgs<T> &, int, int, int, const double *, const double *, \
                                      double, const T *, const T *, hipStream_t);                         \
-  template void launch_scale_fn<T>(const uint8_t *, const double *, const double *, const double *,    \
-                                   const double *, const double *, const double *, bool, int,          \
-                                   uint8_t *, T *, T *, T *, T *, T *, hipStream_t);                   \
+  template void launch_scale_fns<T>(const uint8_t *, const double *, const double *, int, uint8_t *,   \
+                                    T *, const uint8_t *, const double *, const double *, int,         \
+                                    uint8_t *, T *, hipStream_t);                                      \
+  template void launch_start_state<T>(T *, size_t, Ctrl *, const Ctrl &, hipStream_t);                 \
   template void launch_unscale<T>(const IterArgs<T> &, const double *, const double *,                 \
                                   const uint8_t *, const double *, const double *, const double *,     \
                                   const double *, const double *, const uint8_t *, const double *,     \

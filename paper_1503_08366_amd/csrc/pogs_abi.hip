@@ -215,7 +215,6 @@ template <typename T> int alloc_iteration(pogs_ctx *c) {
   const size_t o_slots = cv.take((size_t)nslots * 8);
   const size_t o_cnt = cv.take((size_t)(ntiles + 64) * sizeof(unsigned));
   const size_t o_ctrl = cv.take(sizeof(Ctrl));
-  const size_t o_obj = cv.take(64);
   char *base;
   int rc;
   if ((rc = c->arena.alloc((void **)&base, cv.off))) return rc;
@@ -233,7 +232,6 @@ template <typename T> int alloc_iteration(pogs_ctx *c) {
   c->slots = (double *)(base + o_slots);
   c->counters = (unsigned *)(base + o_cnt);
   c->ctrl = (Ctrl *)(base + o_ctrl);
-  c->obj_dev = (double *)(base + o_obj);
   POGS_HIP_TRY(hipMemsetAsync(c->vec, 0, c->vec_elems() * sizeof(T), c->stream));
   POGS_HIP_TRY(hipMemsetAsync(c->counters, 0, (size_t)(ntiles + 64) * sizeof(unsigned), c->stream));
   c->ctrl_host = (Ctrl *)pinned_slab().get();
@@ -602,12 +600,7 @@ template <typename T> int upload_fns(pogs_ctx *c, const pogs_fn *f, const pogs_f
   const hipError_t e = hipMemcpyAsync(c->fn_raw, st, c->fn_bytes, hipMemcpyHostToDevice, s);
   pinned_stage().release(s);
   if (e != hipSuccess) return POGS_EDEVICE;
-  T *fsp = (T *)c->fs, *gsp = (T *)c->gs;
-  // f^(y) = f(y / D), g^(x) = g(E x)  (Section 4.1)
-  launch_scale_fn<T>(c->fh0, c->f0, c->f0 + m, c->f0 + 2 * m, c->f0 + 3 * m, c->f0 + 4 * m, c->D, true, m, c->fh, fsp,
-                     fsp + m, fsp + 2 * m, fsp + 3 * m, fsp + 4 * m, s);
-  launch_scale_fn<T>(c->gh0, c->g0, c->g0 + n, c->g0 + 2 * n, c->g0 + 3 * n, c->g0 + 4 * n, c->E, false, n, c->gh, gsp,
-                     gsp + n, gsp + 2 * n, gsp + 3 * n, gsp + 4 * n, s);
+  launch_scale_fns<T>(c->fh0, c->f0, c->D, m, c->fh, (T *)c->fs, c->gh0, c->g0, c->E, n, c->gh, (T *)c->gs, s);
   return POGS_OK;
 }
 
@@ -818,25 +811,6 @@ template <typename T> int solve_impl(pogs_ctx *c, const pogs_fn *f, const pogs_f
   auto start = [&](bool fused) -> int {
     c->fused = fused;
     c->cg_one_pass = cg_cap > 0 && c->cg_blocks > 0;
-    // zero state (Algorithm 1 starts from x = y = x~ = y~ = 0), or the warm start
-    POGS_HIP_TRY(hipMemsetAsync(c->vec, 0, c->vec_elems() * sizeof(T), s));
-    if (x0 || nu0) {
-      const T *dx0 = (const T *)x0, *dnu0 = (const T *)nu0;
-      if (out->mem == POGS_HOST) {  // staged in the output vectors (written again at the end)
-        if (x0) {
-          POGS_HIP_TRY(hipMemcpyAsync(c->vecp<T>(11), x0, (size_t)n * sizeof(T), hipMemcpyHostToDevice, s));
-          dx0 = c->vecp<T>(11);
-        }
-        if (nu0) {
-          POGS_HIP_TRY(hipMemcpyAsync(c->vecp<T>(14), nu0, (size_t)m * sizeof(T), hipMemcpyHostToDevice, s));
-          dnu0 = c->vecp<T>(14);
-        }
-      }
-      if (c->sparse) launch_warm_start_sparse<T>(c->iter_args<T>(), c->D, c->E, p.rho0, dx0, dnu0, s);
-      else launch_warm_start<T>(c->iter_args<T>(), c->splits, c->rps, c->ncolp, c->D, c->E, p.rho0, dx0, dnu0, s);
-      if (cg_cap > 0) launch_cg_from_state<T>(c->iter_args<T>(), s);
-      if (out->mem == POGS_HOST) POGS_HIP_TRY(hipStreamSynchronize(s));  // host x0, nu0 may be pageable
-    }
     Ctrl h{};
     h.eps_abs = p.eps_abs;
     h.eps_rel = p.eps_rel;
@@ -854,8 +828,26 @@ template <typename T> int solve_impl(pogs_ctx *c, const pogs_fn *f, const pogs_f
     h.stop_gap = gap;
     h.cg.stop = -1;
     h.res_e1 = h.res_e2 = c->res_epoch;
+    // zero state (Algorithm 1 starts from x = y = x~ = y~ = 0), or the warm start
     *c->ctrl_host = h;
-    POGS_HIP_TRY(hipMemcpyAsync(c->ctrl, c->ctrl_host, sizeof(Ctrl), hipMemcpyHostToDevice, s));
+    launch_start_state<T>((T *)c->vec, c->vec_elems(), c->ctrl, h, s);
+    if (x0 || nu0) {
+      const T *dx0 = (const T *)x0, *dnu0 = (const T *)nu0;
+      if (out->mem == POGS_HOST) {  // staged in the output vectors (written again at the end)
+        if (x0) {
+          POGS_HIP_TRY(hipMemcpyAsync(c->vecp<T>(11), x0, (size_t)n * sizeof(T), hipMemcpyHostToDevice, s));
+          dx0 = c->vecp<T>(11);
+        }
+        if (nu0) {
+          POGS_HIP_TRY(hipMemcpyAsync(c->vecp<T>(14), nu0, (size_t)m * sizeof(T), hipMemcpyHostToDevice, s));
+          dnu0 = c->vecp<T>(14);
+        }
+      }
+      if (c->sparse) launch_warm_start_sparse<T>(c->iter_args<T>(), c->D, c->E, p.rho0, dx0, dnu0, s);
+      else launch_warm_start<T>(c->iter_args<T>(), c->splits, c->rps, c->ncolp, c->D, c->E, p.rho0, dx0, dnu0, s);
+      if (cg_cap > 0) launch_cg_from_state<T>(c->iter_args<T>(), s);
+      if (out->mem == POGS_HOST) POGS_HIP_TRY(hipStreamSynchronize(s));  // host x0, nu0 may be pageable
+    }
     return POGS_OK;
   };
   bool stepwise = true;  // one launch per step of an iteration
@@ -874,20 +866,26 @@ template <typename T> int solve_impl(pogs_ctx *c, const pogs_fn *f, const pogs_f
   const int last_set = c->fused ? ((c->ctrl_host->st[0].k - 1) & 1) : 0;
   const IterArgs<T> ia = c->iter_args<T>(last_set);
   T *xo = c->vecp<T>(11), *yo = c->vecp<T>(12), *muo = c->vecp<T>(13), *nuo = c->vecp<T>(14);
+  double *obj = c->obj_host;
+  const PinnedOut direct(out->mem == POGS_HOST ? 2 * (size_t)(m + n) * sizeof(T) : PinnedOut::kBytes + 1);
   if (out->mem == POGS_DEVICE) {
     xo = (T *)out->x;
     yo = (T *)out->y;
     muo = (T *)out->mu;
     nuo = (T *)out->nu;
+  } else if (direct.p) {
+    xo = (T *)direct.p;
+    yo = xo + n;
+    muo = yo + m;
+    nuo = muo + n;
   }
   double *fa = c->f0, *ga = c->g0;
   const CtrlState &fin = c->ctrl_host->st[0];
   launch_unscale<T>(ia, c->D, c->E, c->fh0, fa, fa + m, fa + 2 * m, fa + 3 * m, fa + 4 * m, c->gh0, ga, ga + n,
                     ga + 2 * n, ga + 3 * n, ga + 4 * n, xo, yo, muo, nuo, ia.s_gconj + ia.nbx + ia.nby,
-                    c->obj_dev, c->counters + (int)cdiv(n, gemv_t_tile(sizeof(T))) + 8, fin.by_gap,
+                    obj, c->counters + (int)cdiv(n, gemv_t_tile(sizeof(T))) + 8, fin.by_gap,
                     fin.rho, s);
-  POGS_HIP_TRY(hipMemcpyAsync(c->obj_host, c->obj_dev, sizeof(double), hipMemcpyDeviceToHost, s));
-  if (out->mem == POGS_HOST) {
+  if (out->mem == POGS_HOST && !direct.p) {
     if (out->x) POGS_HIP_TRY(hipMemcpyAsync(out->x, xo, (size_t)n * sizeof(T), hipMemcpyDeviceToHost, s));
     if (out->y) POGS_HIP_TRY(hipMemcpyAsync(out->y, yo, (size_t)m * sizeof(T), hipMemcpyDeviceToHost, s));
     if (out->mu) POGS_HIP_TRY(hipMemcpyAsync(out->mu, muo, (size_t)n * sizeof(T), hipMemcpyDeviceToHost, s));
@@ -895,6 +893,12 @@ template <typename T> int solve_impl(pogs_ctx *c, const pogs_fn *f, const pogs_f
   }
   POGS_HIP_TRY(hipStreamSynchronize(s));
   POGS_HIP_TRY(hipGetLastError());
+  if (direct.p) {
+    if (out->x) memcpy(out->x, xo, (size_t)n * sizeof(T));
+    if (out->y) memcpy(out->y, yo, (size_t)m * sizeof(T));
+    if (out->mu) memcpy(out->mu, muo, (size_t)n * sizeof(T));
+    if (out->nu) memcpy(out->nu, nuo, (size_t)m * sizeof(T));
+  }
   const CtrlState &r = c->ctrl_host->st[0];
   out->optval = *c->obj_host;
   out->r_pri = r.r_pri;
