@@ -57,16 +57,17 @@ __global__ __launch_bounds__(kBlock) void prox_cg_kernel(IterArgs<T> p) {
   if (threadIdx.x == 0) st = p.ctrl->st[1 - par];
   double part[4];
   control_partials(p, 1 - par, part);
+  const CtrlParams cp = ctrl_params(p.ctrl);
   load();
   __syncthreads();
-  if (!st.done && st.pending) control_apply(p, part, st, bs);
+  if (!st.done && st.pending) control_apply(cp, part, st, bs);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     CtrlState out = st;
     out.pending = st.done ? 0 : 1;
     p.ctrl->st[par] = out;
   }
   if (st.done) return;
-  const T rho = (T)st.rho, resc = (T)st.rescale, alpha = (T)p.ctrl->alpha;
+  const T rho = (T)st.rho, resc = (T)st.rescale, alpha = (T)cp.alpha;
   double contrib = 0.0;
   while (i < len) {
     const HalfStep<T> hs = half_step<T>(fh, fa, fb, fc, fd, fe, vi, vti, rho, resc, alpha);

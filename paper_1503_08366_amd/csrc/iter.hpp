@@ -71,9 +71,20 @@ __device__ inline void block_sum4(double v[4], double *scratch /* 4 * waves */) 
     }
 }
 
+// The solve's parameters that the stop test reads.  Kernels load them with
+// their first loads: read where they are used, behind barriers and branches,
+// each cost another round trip to memory on the way to the first result.
+struct CtrlParams {
+  double eps_abs, eps_rel, alpha, delta, tau;
+  int max_iter, adaptive, stop_gap;
+};
+__device__ inline CtrlParams ctrl_params(const Ctrl *c) {
+  return CtrlParams{c->eps_abs, c->eps_rel, c->alpha, c->delta, c->tau, c->max_iter, c->adaptive, c->stop_gap};
+}
+
 // The stopping test (Section 3.4) and Algorithm 3 for iteration st.k with the
 // given residuals and tolerances; updates st.
-__device__ inline void control_decide(const Ctrl &q, CtrlState &st, double r_pri, double eps_pri, double r_dual,
+__device__ inline void control_decide(const CtrlParams &q, CtrlState &st, double r_pri, double eps_pri, double r_dual,
                                       double eps_dual) {
   st.r_pri = r_pri;
   st.r_dual = r_dual;
@@ -110,13 +121,13 @@ __device__ inline void control_decide(const Ctrl &q, CtrlState &st, double r_pri
   st.pending = 0;
 }
 
-template <typename T>
-__device__ void control_apply(const IterArgs<T> &p, double part[4], CtrlState &st, double *lds) {
+__device__ inline void control_apply(const CtrlParams &q, double part[4], CtrlState &st, double *lds) {
   block_sum4(part, lds);
   if (threadIdx.x == 0) {
-    const Ctrl &q = *p.ctrl;
-    control_decide(q, st, sqrt(part[2]), q.eps_abs + q.eps_rel * sqrt(part[1]), sqrt(part[3]),
+    CtrlState s = st;
+    control_decide(q, s, sqrt(part[2]), q.eps_abs + q.eps_rel * sqrt(part[1]), sqrt(part[3]),
                    q.eps_abs + q.eps_rel * sqrt(part[0]));
+    st = s;
   }
   __syncthreads();
 }
@@ -131,8 +142,9 @@ __device__ __forceinline__ void control_preview_body(const IterArgs<T> &p, int p
   if (threadIdx.x == 0) st = p.ctrl->st[par];
   double part[4];
   control_partials(p, par, part);
+  const CtrlParams cp = ctrl_params(p.ctrl);
   __syncthreads();
-  if (!st.done && st.pending) control_apply(p, part, st, bs);
+  if (!st.done && st.pending) control_apply(cp, part, st, bs);
   if (threadIdx.x == 0) p.ctrl->st[1 - par] = st;
 }
 
@@ -175,6 +187,7 @@ __device__ __forceinline__ void prox_body(const Blk &b, const IterArgs<T> &p) {
   if (threadIdx.x == 0) st = p.ctrl->st[1 - par];
   double part[4];
   control_partials(p, 1 - par, part);
+  const CtrlParams cp = ctrl_params(p.ctrl);
   const FnDev<T> &F = xs ? p.g : p.f;
   T *v = xs ? p.x : p.y;
   T *vt = xs ? p.xt : p.yt;
@@ -191,7 +204,7 @@ __device__ __forceinline__ void prox_body(const Blk &b, const IterArgs<T> &p) {
     fe = F.e[i];
   }
   __syncthreads();
-  if (!st.done && st.pending) control_apply(p, part, st, bs);
+  if (!st.done && st.pending) control_apply(cp, part, st, bs);
   if (b.x == 0 && threadIdx.x == 0) {
     CtrlState out = st;
     out.pending = st.done ? 0 : 1;
@@ -200,8 +213,8 @@ __device__ __forceinline__ void prox_body(const Blk &b, const IterArgs<T> &p) {
   if (st.done) return;
   const T rho = (T)st.rho;
   const T resc = (T)st.rescale;
-  const T alpha = (T)p.ctrl->alpha;
-  const bool gap = p.ctrl->stop_gap;
+  const T alpha = (T)cp.alpha;
+  const bool gap = cp.stop_gap;
   double contrib = 0.0, gobj = 0.0, gconj = 0.0;
   if (i < len) {
     const HalfStep<T> hs = half_step<T, GROUPED>(fh, fa, fb, fc, fd, fe, vi, vti, rho, resc, alpha);
@@ -315,10 +328,11 @@ __device__ __forceinline__ void tall_pass1_prox_body(const Blk &b, const IterArg
   }
   double part[4];
   control_partials(p, 1 - par, part);
+  const CtrlParams cp = ctrl_params(p.ctrl);
   V a[8];
   __syncthreads();
   const bool after_iteration = st.pending != 0;  // an iteration ran before this one in the solve
-  if (!st.done && st.pending) control_apply(p, part, st, bs);
+  if (!st.done && st.pending) control_apply(cp, part, st, bs);
   // the previous iteration's one-pass kernel computed this step with the rho
   // Algorithm 3 has just chosen (and the matching rescale): its results stand
   const bool spec = after_iteration && !st.done && st.rho == spec_rho;
@@ -335,7 +349,7 @@ __device__ __forceinline__ void tall_pass1_prox_body(const Blk &b, const IterArg
   const bool pre = colok && r0 + w + 28 < c1_first;
   if (pre) group_load(a, r0 + w);
   prox_load(r0, c1_first);
-  const T rho = (T)st.rho, resc = (T)st.rescale, alpha = (T)p.ctrl->alpha;
+  const T rho = (T)st.rho, resc = (T)st.rescale, alpha = (T)cp.alpha;
   const bool store = tile == 0;
 
   double acc[2][VN];

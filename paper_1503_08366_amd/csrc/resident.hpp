@@ -196,10 +196,10 @@ __device__ __forceinline__ void resident_body(const ResArgs<T> &p, char *smem) {
   };
   if (p.ctrl->res_failed) return fail();
   if (st.done) return;
-  const Ctrl &qc = *p.ctrl;
+  const CtrlParams qc = ctrl_params(p.ctrl);
   const double eps_abs = qc.eps_abs, eps_rel = qc.eps_rel;
   const T alpha = (T)qc.alpha;
-  unsigned e1 = qc.res_e1, e2 = qc.res_e2;
+  unsigned e1 = p.ctrl->res_e1, e2 = p.ctrl->res_e2;
 
   // the wave's rows; rows past L and pieces past ld are zero
   V a[RPW][NC], kin[KR][NC];
