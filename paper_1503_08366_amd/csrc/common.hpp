@@ -163,6 +163,26 @@ __device__ inline double block_sum(double v, double *scratch) {
   return t;
 }
 
+// Four block-wide sums at once (one barrier pair); results valid in thread 0.
+// Fixed order: wave shuffle tree, then the waves in index order.
+__device__ inline void block_sum4(double v[4], double *scratch /* 4 * waves */) {
+  const int nw = blockDim.x / kWave, w = threadIdx.x / kWave;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) v[c] = wave_sum(v[c]);
+  __syncthreads();
+  if ((threadIdx.x & (kWave - 1)) == 0)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) scratch[c * nw + w] = v[c];
+  __syncthreads();
+  if (threadIdx.x == 0)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      double t = 0.0;
+      for (int i = 0; i < nw; ++i) t += scratch[c * nw + i];
+      v[c] = t;
+    }
+}
+
 // Loads of data written by other workgroups of the same launch: read at
 // device (agent) scope so no stale cache line is returned.
 __device__ inline double load_agent(const double *p) {

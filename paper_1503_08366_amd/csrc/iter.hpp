@@ -51,26 +51,6 @@ __device__ inline void control_partials(const IterArgs<T> &p, int spar, double p
   part[3] = slot_partial(p.s_dual, p.n_dual);
 }
 
-// Four block-wide sums at once (one barrier pair); results valid in thread 0.
-// Fixed order: wave shuffle tree, then the waves in index order.
-__device__ inline void block_sum4(double v[4], double *scratch /* 4 * waves */) {
-  const int nw = blockDim.x / kWave, w = threadIdx.x / kWave;
-#pragma unroll
-  for (int c = 0; c < 4; ++c) v[c] = wave_sum(v[c]);
-  __syncthreads();
-  if ((threadIdx.x & (kWave - 1)) == 0)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) scratch[c * nw + w] = v[c];
-  __syncthreads();
-  if (threadIdx.x == 0)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      double t = 0.0;
-      for (int i = 0; i < nw; ++i) t += scratch[c * nw + i];
-      v[c] = t;
-    }
-}
-
 // The solve's parameters that the stop test reads.  Kernels load them with
 // their first loads: read where they are used, behind barriers and branches,
 // each cost another round trip to memory on the way to the first result.

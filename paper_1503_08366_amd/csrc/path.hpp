@@ -26,7 +26,7 @@ struct PathArgs {
   double *s_mu, *s_yh, *s_pri, *s_dual;     // [blocks][Rp] partial sums
   double *rho, *rescale, *r_pri, *r_dual, *eps_pri, *eps_dual;  // per problem
   int *l, *u, *iters, *done, *status;       // per problem
-  int *all_done;
+  int *all_done, *live;                     // every problem has stopped; problems still running
 };
 
 void path_geometry(PathArgs *p, int *s1, int *s2, int *s3);

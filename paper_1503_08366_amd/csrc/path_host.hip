@@ -180,6 +180,7 @@ extern "C" int pogs_solve_path(pogs_ctx *ctx, int32_t R, const pogs_fn *f, const
   p.done = ints + 3 * Rp;
   p.status = ints + 4 * Rp;
   p.all_done = ints + 5 * Rp;
+  p.live = p.all_done + 1;
   {
     std::vector<double> hc(6 * (size_t)Rp, 0.0);
     for (int r = 0; r < Rp; ++r) {
@@ -188,6 +189,7 @@ extern "C" int pogs_solve_path(pogs_ctx *ctx, int32_t R, const pogs_fn *f, const
     }
     std::vector<int> hi(5 * (size_t)Rp + 64, 0);
     for (int r = 0; r < Rp; ++r) hi[4 * Rp + r] = -1;
+    hi[5 * Rp + 1] = R;  // live
     POGS_HIP_TRY(hipMemcpyAsync(percol, hc.data(), hc.size() * 8, hipMemcpyHostToDevice, s));
     POGS_HIP_TRY(hipMemcpyAsync(ints, hi.data(), hi.size() * 4, hipMemcpyHostToDevice, s));
     POGS_HIP_TRY(hipStreamSynchronize(s));
