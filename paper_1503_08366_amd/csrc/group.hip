@@ -51,7 +51,7 @@ __global__ __launch_bounds__(256) void g_layout_tiles(const GProb *probs, const 
 template <int U>
 __global__ __launch_bounds__(kBlock) void g_eq_sweep(const GProb *probs, const GItem *items) {
   GROUP_ITEM();
-  equil_sweep_body<U, 4>(b, P.it.A, P.it.m, P.it.n, P.it.ld, P.eq_rps, P.e, P.d, P.eq_part, P.eq_ncolp, P.nf,
+  equil_sweep_body<float, U, 4>(b, P.it.A, P.it.m, P.it.n, P.it.ld, P.eq_rps, P.e, P.d, P.eq_part, P.eq_ncolp, P.nf,
                          P.gamma_m);
 }
 

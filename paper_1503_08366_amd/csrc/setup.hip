@@ -65,12 +65,35 @@ void launch_layout(const void *src, pogs_dtype sdt, pogs_order ord, int64_t lda,
 // ---------------------------------------------------------------------------
 
 
-template <int U, int R>
-__global__ __launch_bounds__(kBlock) void equil_sweep_kernel(const float *__restrict__ A, int m, int n, int ld,
-                                                             int rps, const double *__restrict__ e,
-                                                             double *__restrict__ d, double *__restrict__ part,
-                                                             int ncolp, double nf, double gamma_m) {
-  equil_sweep_body<U, R>(hw_block(), A, m, n, ld, rps, e, d, part, ncolp, nf, gamma_m);
+template <typename T, int U, int R>
+__global__ __launch_bounds__(kBlock) void equil_sweep_kernel(const T *__restrict__ A, int m, int n, int ld, int rps,
+                                                             const double *__restrict__ e, double *__restrict__ d,
+                                                             double *__restrict__ part, int ncolp, double nf,
+                                                             double gamma_m) {
+  equil_sweep_body<T, U, R>(hw_block(), A, m, n, ld, rps, e, d, part, ncolp, nf, gamma_m);
+}
+
+// All sweeps, one pass over A each: as many workgroups as are resident at once
+// (no tail round).  False if the workspace does not hold their partial sums.
+template <typename T, int U, int R>
+bool equil_sweeps(const T *A, int m, int n, int ld, int iters, const EqArgs &a, double *part, size_t part_doubles,
+                  int ncolp, hipStream_t s) {
+  // fewer where a workgroup's rows are worth more than its share of the partial
+  // sums that the finish adds (float64 3000 x 700, whole setup without a factor:
+  // 207 us with 750, 185 with 375; float32 1000 x 5000: 290 with 500, 246 with 250)
+  const int most = std::is_same<T, double>::value ? 512 : U <= 4 ? 1024 : 256;
+  const int nwg = (int)std::min<int64_t>(
+      std::min(most, resident_workgroups((const void *)equil_sweep_kernel<T, U, R>, kBlock)), cdiv(m, R));
+  const int rps = (int)round_up(cdiv(m, nwg), R);
+  const int nsplit = (int)cdiv(m, rps);
+  if ((size_t)nsplit * ncolp > part_doubles) return false;
+  for (int it = 0; it < iters; ++it) {
+    hipLaunchKernelGGL((equil_sweep_kernel<T, U, R>), dim3(nsplit), dim3(kBlock), 0, s, A, m, n, ld, rps, a.e, a.d, part,
+                       ncolp, a.nf, a.gamma_m);
+    hipLaunchKernelGGL((gemv_t_finish_kernel<1, EpiEqCol>), dim3(cdiv(n, kFinishCols)), dim3(kBlock), 0, s, n, nsplit,
+                       (const double *)part, ncolp, EpiEqCol{a});
+  }
+  return true;
 }
 
 __global__ void fill_kernel(double *p, double v, int len) {
@@ -139,45 +162,23 @@ int run_equilibrate(T *A, int m, int n, int ld, int iters, double eps_cmp, doubl
   hipLaunchKernelGGL(fill_kernel, dim3(cdiv(n, 256)), dim3(256), 0, s, a.e, 1.0, n);
   const int tiles = (int)cdiv(n, gemv_t_tile(sizeof(T)));
   (void)counters;
-  if (sizeof(T) == 4 && n <= 4096) {
-    // fused sweeps: one pass over A per sweep, as many workgroups as are
-    // resident at once (no tail round)
-    constexpr int R = 4;
-    const int U = (int)cdiv(n, 1024);
-    const void *kern = U == 1   ? (const void *)equil_sweep_kernel<1, R>
-                       : U == 2 ? (const void *)equil_sweep_kernel<2, R>
-                       : U == 3 ? (const void *)equil_sweep_kernel<3, R>
-                                : (const void *)equil_sweep_kernel<4, R>;
-    const int nwg = (int)std::min<int64_t>(std::min(1024, resident_workgroups(kern, kBlock)), cdiv(m, R));
-    const int rps = (int)round_up(cdiv(m, nwg), R);
-    const int nsplit = (int)cdiv(m, rps);
-    if ((size_t)((part + (size_t)nsplit * ncolp) - ws) * sizeof(double) > ws_bytes) return POGS_ENOMEM;
-    for (int it = 0; it < iters; ++it) {
-      const float *Af = (const float *)A;
-      switch (U) {
-        case 1:
-          hipLaunchKernelGGL((equil_sweep_kernel<1, R>), dim3(nsplit), dim3(kBlock), 0, s, Af, m, n, ld, rps, a.e,
-                             a.d, part, ncolp, a.nf, a.gamma_m);
-          break;
-        case 2:
-          hipLaunchKernelGGL((equil_sweep_kernel<2, R>), dim3(nsplit), dim3(kBlock), 0, s, Af, m, n, ld, rps, a.e,
-                             a.d, part, ncolp, a.nf, a.gamma_m);
-          break;
-        case 3:
-          hipLaunchKernelGGL((equil_sweep_kernel<3, R>), dim3(nsplit), dim3(kBlock), 0, s, Af, m, n, ld, rps, a.e,
-                             a.d, part, ncolp, a.nf, a.gamma_m);
-          break;
-        default:
-          hipLaunchKernelGGL((equil_sweep_kernel<4, R>), dim3(nsplit), dim3(kBlock), 0, s, Af, m, n, ld, rps, a.e,
-                             a.d, part, ncolp, a.nf, a.gamma_m);
-          break;
-      }
-      EpiEqCol ec{a};
-      hipLaunchKernelGGL((gemv_t_finish_kernel<1, EpiEqCol>), dim3(cdiv(n, kFinishCols)), dim3(kBlock), 0, s, n,
-                         nsplit, (const double *)part, ncolp, ec);
-    }
-  }
-  for (int it = 0; it < iters && !(sizeof(T) == 4 && n <= 4096); ++it) {
+  const size_t part_doubles = ws_bytes / sizeof(double) - (size_t)(part - ws);
+  // Sweeps of one pass over A where a workgroup holds a row's columns in
+  // registers (6144 in float32, 3072 in float64), else two passes.  Whole setup
+  // without a factor, two passes -> one: float64 200 x 100 197 -> 164 us,
+  // 4000 x 2000 428 -> 283, 20000 x 1000 681 -> 477; float32 12000 x 5000
+  // 1061 -> 759.
+  constexpr int CU = kBlock * Vec16<T>::N;
+  const int U = (int)cdiv(n, CU);
+  bool fused = true, room = true;
+  if (U == 1) room = equil_sweeps<T, 1, 4>(A, m, n, ld, iters, a, part, part_doubles, ncolp, s);
+  else if (U == 2) room = equil_sweeps<T, 2, 4>(A, m, n, ld, iters, a, part, part_doubles, ncolp, s);
+  else if (U == 3) room = equil_sweeps<T, 3, 4>(A, m, n, ld, iters, a, part, part_doubles, ncolp, s);
+  else if (U == 4) room = equil_sweeps<T, 4, 4>(A, m, n, ld, iters, a, part, part_doubles, ncolp, s);
+  else if (U <= 6) room = equil_sweeps<T, 6, 2>(A, m, n, ld, iters, a, part, part_doubles, ncolp, s);
+  else fused = false;
+  if (!room) return POGS_ENOMEM;
+  for (int it = 0; it < iters && !fused; ++it) {
     // rows: d = n / (|A|^2 e + gamma/m)
     {
       EpiEqRow er{a};

@@ -81,41 +81,42 @@ struct EpiEqCol {
 };
 
 // One Sinkhorn-Knopp sweep (Algorithm 2, p = 2) in a single pass over a
-// float32 A with n <= 1024 U: workgroup b owns rows [b rps, (b + 1) rps) and
-// thread t the columns 4 t + 1024 u.  For each group of R rows the row sums
+// A with n <= 1024 U (float32; 512 U in float64): workgroup b owns rows
+// [b rps, (b + 1) rps) and thread t the columns 4 t + 1024 u (2 t + 512 u).  For each group of R rows the row sums
 // sum_j A_ij^2 e_j are reduced across the workgroup (fixed order: lane tree,
 // then waves in order), every thread forms d_i = n / (sum + gamma/m) and adds
 // A_ij^2 d_i to its column sums while the row is still in registers.  The
 // column sums of each workgroup go to part[b * ncolp + j]; a finish kernel
 // adds them in workgroup order and forms e.  Same arithmetic as the two-pass
 // sweep, half the reads of A.
-template <int U, int R>
-__device__ __forceinline__ void equil_sweep_body(const Blk &b, const float *__restrict__ A, int m, int n, int ld,
+template <typename T, int U, int R>
+__device__ __forceinline__ void equil_sweep_body(const Blk &b, const T *__restrict__ A, int m, int n, int ld,
                                                  int rps, const double *__restrict__ e, double *__restrict__ d,
                                                  double *__restrict__ part, int ncolp, double nf, double gamma_m) {
-  typedef float f4 __attribute__((ext_vector_type(4)));
+  using V = typename Vec16<T>::type;
+  constexpr int VN = Vec16<T>::N, CU = kBlock * VN;
   __shared__ double red[2][R][kBlock / kWave];
   const int t = threadIdx.x, lane = t & (kWave - 1), w = t >> 6;
   const int r0 = b.x * rps, r1 = min(m, r0 + rps);
-  double ev[U][4], col[U][4];
+  double ev[U][VN], col[U][VN];
 #pragma unroll
   for (int u = 0; u < U; ++u)
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int c = 4 * t + 1024 * u + k;
+    for (int k = 0; k < VN; ++k) {
+      const int c = VN * t + CU * u + k;
       ev[u][k] = c < n ? e[c] : 0.0;
       col[u][k] = 0.0;
     }
   int g = 0;
   for (int i0 = r0; i0 < r1; i0 += R, ++g) {
-    f4 a[R][U];
+    V a[R][U];
 #pragma unroll
     for (int ri = 0; ri < R; ++ri) {
       const int row = min(i0 + ri, r1 - 1);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int c = 4 * t + 1024 * u;
-        a[ri][u] = c < ld ? *reinterpret_cast<const f4 *>(A + (size_t)row * ld + c) : f4{0.f, 0.f, 0.f, 0.f};
+        const int c = VN * t + CU * u;
+        a[ri][u] = c < ld ? *reinterpret_cast<const V *>(A + (size_t)row * ld + c) : V{};
       }
     }
     double p[R];
@@ -125,7 +126,7 @@ __device__ __forceinline__ void equil_sweep_body(const Blk &b, const float *__re
 #pragma unroll
       for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < VN; ++k) {
           const double x = (double)a[ri][u][k];
           acc = fma(x * x, ev[u][k], acc);
         }
@@ -144,7 +145,7 @@ __device__ __forceinline__ void equil_sweep_body(const Blk &b, const float *__re
 #pragma unroll
       for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < VN; ++k) {
           const double x = (double)a[ri][u][k];
           col[u][k] = fma(x * x, di, col[u][k]);
         }
@@ -153,8 +154,8 @@ __device__ __forceinline__ void equil_sweep_body(const Blk &b, const float *__re
 #pragma unroll
   for (int u = 0; u < U; ++u)
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int c = 4 * t + 1024 * u + k;
+    for (int k = 0; k < VN; ++k) {
+      const int c = VN * t + CU * u + k;
       if (c < ncolp) part[(size_t)b.x * ncolp + c] = col[u][k];
     }
 }
