@@ -171,9 +171,8 @@ template <typename T, bool PENDING = true>
 __device__ bool cg_rows_enter(const IterArgs<T> &p, int j, int cap, EpiCgRows<T> *e) {
   __shared__ double sc[kCgWaves];
   Ctrl &q = *p.ctrl;
-  if (q.st[p.par].done) return false;
-  const int stop = q.cg.stop;
-  if (stop >= 0 && stop < j) return false;  // stopped at an earlier step
+  const int done = q.st[p.par].done, stop = q.cg.stop;  // one round trip: most launches end here
+  if (done != 0 | (stop >= 0 && stop < j)) return false;  // or stopped at an earlier step
   const double gam = block_total(p.s_gam + (size_t)(j & 1) * p.n_dual, p.n_dual, sc);
   const double alpha_prev = j > 0 ? q.cg.alpha : 0.0;
   const double thr2 = q.cg.thr2;
@@ -234,7 +233,7 @@ template <typename T> struct EpiCgStep {
 template <typename T> __device__ bool cg_step_enter(const IterArgs<T> &p, int j, EpiCgStep<T> *e) {
   __shared__ double sc[kCgWaves];
   Ctrl &q = *p.ctrl;
-  if (q.st[p.par].done || q.cg.stop >= 0) return false;
+  if ((q.st[p.par].done != 0) | (q.cg.stop >= 0)) return false;
   const double qq = block_total(p.s_qq, p.n_pri, sc);
   const double gam = q.cg.gamma[j & 1];
   double beta = 0.0, pn2 = gam;

@@ -96,20 +96,22 @@ constexpr int kCappedBlocks = 1024;
 __host__ __device__ inline int capped_blocks(int blocks) { return blocks < kCappedBlocks ? blocks : kCappedBlocks; }
 
 // A sparse float32 matrix split by columns into nseg segments of seg columns,
-// as many as fit in a workgroup's LDS (pieces.hip): the entries of row r in
-// segment s are [rp[s rows + r], rp[s rows + r + 1]) of va and of ci, ci the
-// column inside its segment.  A workgroup takes `tile` rows and one of `groups`
-// equal runs of segments.  rp == nullptr: the context has no such copy.
+// as many as fit in a workgroup's LDS (pieces.hip), segment after segment, and in
+// a segment row after row; ci is the column inside its segment.  The entries of
+// rows 64 b .. 64 b + 63 in segment s begin at base[s blocks + b], those of row r
+// off[64 s blocks + r] further on (rows past the last have the block's end).  A
+// workgroup takes `tile` rows and one of `groups` equal runs of segments.
+// va == nullptr: the context has no such copy.
 constexpr int kPcWaves = 16;                 // waves of a workgroup
 constexpr int kPcRpl = 8;                    // rows per lane at most
 constexpr int kPcTile = kPcWaves * 64 * kPcRpl;
 constexpr int kPcSeg = 32128;                // columns per segment at most
 constexpr int kPcPad = 256;                  // entries that may be read past the last
 struct SpPieces {
-  int *rp;
-  uint16_t *ci;
+  int *base;
+  uint16_t *off, *ci;
   float *va;
-  int rows, cols, seg, nseg, tile, tiles, groups;
+  int rows, blocks, cols, seg, nseg, tile, tiles, groups;
 };
 
 // Workgroups of the one-pass tall iteration (tall_one_pass_body) for an m x n
@@ -300,12 +302,15 @@ template <typename T>
 void run_equilibrate_sparse(Csr<T> A, Csr<T> At, int m, int n, int iters, double eps_cmp, double *D, double *E,
                             double *ws, hipStream_t s);
 // The copies in pieces (pieces.hip).  pieces_shape: false where the row
-// passes over the plain copy are used instead.  fill_pieces: rp, ci and va of
-// P from the scaled A; cur holds nseg rows int, sums pieces_sums(P) int.
+// passes over the plain copy are used instead.  fill_pieces: the arrays of P
+// from the scaled A; rp holds nseg rows + 1 int, cur nseg rows int, sums
+// pieces_sums(P) int; *too_long is set where the entries of 64 rows in one
+// segment exceed 16 bits (the pieces are then not to be used).
 // launch_pc_*: the passes of a projection (start, one CG step, its rows alone).
 bool pieces_shape(int64_t rows, int64_t cols, int64_t nnz, int groups, SpPieces *P);
 int64_t pieces_sums(const SpPieces &P);
-void fill_pieces(const Csr<float> &A, const SpPieces &P, int64_t nnz, int *cur, int *sums, hipStream_t s);
+void fill_pieces(const Csr<float> &A, const SpPieces &P, int64_t nnz, int *rp, int *cur, int *sums,
+                 unsigned *too_long, hipStream_t s);
 int pieces_finish_blocks(int n);
 void launch_pc_first(const IterArgs<float> &p, int ncolp, hipStream_t s);
 void launch_pc_rows(const IterArgs<float> &p, int j, int cap, hipStream_t s);

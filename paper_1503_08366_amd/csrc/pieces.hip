@@ -7,11 +7,13 @@
 // in flight): each 4-byte gather moves a 128-byte line through a CU's L1, while
 // the entries themselves need 50 us of HBM.
 //
-// Measured, 2000000 x 200000, 16 entries a row: A^ s 245 -> 76 us, A^T r1 255
-// -> 85 (the entries, row bounds and partial sums are 280 and 300 MB), a CG step
-// 500 -> 188, a Lasso 336 -> 147 ms.  Of a pass, adding up the products takes
+// Measured, 2000000 x 200000, 16 entries a row: A^ s 245 -> 70 us, A^T r1 255
+// -> 79 (the entries, row bounds and partial sums are 255 and 250 MB), a CG step
+// 500 -> 180, a Lasso 336 -> 132 ms.  Of a pass, adding up the products takes
 // about 12 us, refilling the segments 5, the gathers 2.  Two groups of entries on
-// the way: 1 and 3 are 1 and 6 % slower (3 runs out of registers).
+// the way: 1 and 3 are 1 and 6 % slower (3 runs out of registers).  The bounds of
+// the rows are 16 bits each from their block's: as 32-bit ones they were 50 MB of
+// a pass, and a step 189 us.
 //
 // A workgroup (16 waves, one per CU: the segment takes most of the LDS) owns
 // up to kPcTile rows; a wave takes 64 of them at a time, one per lane, for each
@@ -35,6 +37,8 @@ namespace {
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef unsigned short u4 __attribute__((ext_vector_type(4)));
 typedef double d2 __attribute__((ext_vector_type(2)));
+// memory that no kernel writes while it is read: uniform loads go to scalar registers
+#define KernelConst __attribute__((address_space(4)))
 
 constexpr int kPcThreads = kPcWaves * 64;
 constexpr int kPcChunk = 256;  // entries a wave handles at once, 4 per lane
@@ -64,21 +68,23 @@ __device__ __forceinline__ void pieces_body(const SpPieces &A, int tile, int sg0
   for (int g = 0; g < kPcRpl; ++g) acc[g] = 0.0;
   for (int sg = sg0; sg < sg1; ++sg) {
     const int c0 = sg * A.seg, len = min(A.seg, A.cols - c0);
-    const int *rp = A.rp + (size_t)sg * A.rows;
+    const KernelConst int *base = (const KernelConst int *)(uintptr_t)(A.base + (size_t)sg * A.blocks);
+    const uint16_t *off = A.off + (size_t)sg * A.blocks * 64;
     f4 st[kPcSegLoads];
 #pragma unroll
     for (int u = 0; u < kPcSegLoads; ++u) {
       const int t = (u * kPcThreads + threadIdx.x) * 4;
       if (t < len) st[u] = src(c0 + t);
     }
-    // where every row's entries begin (lanes past the last row: where it ends);
-    // a lane's entries end where the next lane's begin
-    int lo[kPcRpl], ends[kPcRpl];
+    // where a block's entries begin and end, and every row's from there; a lane's
+    // entries end where the next lane's begin (blocks past the tile repeat its last)
+    int begin[kPcRpl], ends[kPcRpl], lo[kPcRpl];
 #pragma unroll
     for (int g = 0; g < kPcRpl; ++g) {
-      const int rb = r0 + (g * kPcWaves + w) * 64;
-      lo[g] = rp[min(rb + lane, r1)];
-      ends[g] = rp[min(rb + 64, r1)];
+      const int b = min(r0 + (g * kPcWaves + w) * 64, r1 - 1) >> 6;
+      begin[g] = base[b];
+      ends[g] = base[b + 1];
+      lo[g] = off[b * 64 + lane];
     }
     __syncthreads();  // the last segment has been read
 #pragma unroll
@@ -97,7 +103,7 @@ __device__ __forceinline__ void pieces_body(const SpPieces &A, int tile, int sg0
         jv = *reinterpret_cast<const u4 *>(A.ci + kk);
       }
     };
-    auto first = [&](int g) { return __builtin_amdgcn_readfirstlane(lo[g]) & ~3; };
+    auto first = [&](int g) { return begin[g] & ~3; };
 #pragma unroll
     for (int g = 0; g < kPcAhead; ++g) load(first(g), ends[g], a[g], j[g]);
     __syncthreads();
@@ -107,7 +113,8 @@ __device__ __forceinline__ void pieces_body(const SpPieces &A, int tile, int sg0
       constexpr int R = kPcAhead + 1;
       if (g + kPcAhead < kPcRpl) load(first(g + kPcAhead), ends[g + kPcAhead], a[(g + kPcAhead) % R], j[(g + kPcAhead) % R]);
       const int kb = first(g), ke = ends[g];
-      const int next = __shfl_down(lo[g], 1), hi = lane == 63 ? ke : next;
+      const int next = __shfl_down(lo[g], 1);
+      const int from = begin[g] + lo[g], hi = lane == 63 ? ke : begin[g] + next;
       f4 av = a[g % R];
       u4 jv = j[g % R];
       double s = 0.0;
@@ -121,7 +128,7 @@ __device__ __forceinline__ void pieces_body(const SpPieces &A, int tile, int sg0
         reinterpret_cast<d2 *>(pw)[2 * lane + 1] = p1;
         wave_lds_order();
         const int q1 = min(hi - k, kPcChunk);
-        for (int q = max(lo[g] - k, 0); q < q1; q += 4) {
+        for (int q = max(from - k, 0); q < q1; q += 4) {
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             const double t = pw[q + u];
@@ -232,7 +239,7 @@ __global__ __launch_bounds__(kPcThreads) void pc_first_kernel(IterArgs<float> p,
 // A^T r1 after the update of step j
 __global__ __launch_bounds__(kPcThreads) void pc_step_kernel(IterArgs<float> p, int ncolp) {
   __shared__ PcLds lds;
-  if (p.ctrl->st[p.par].done || p.ctrl->cg.stop >= 0) return;
+  if ((p.ctrl->st[p.par].done != 0) | (p.ctrl->cg.stop >= 0)) return;
   pieces_cols_pass(p.pat, SrcVec{p.yt}, 0, p.part, ncolp, lds);
 }
 
@@ -259,7 +266,7 @@ __global__ __launch_bounds__(kBlock) void pc_first_finish_kernel(IterArgs<float>
 // alpha_j is stored and in r1 already (the second sum is 0).
 __global__ __launch_bounds__(kBlock) void pc_step_finish_kernel(IterArgs<float> p, int j, int ncolp) {
   const Ctrl &q = *p.ctrl;
-  if (q.st[p.par].done || q.cg.stop >= 0) return;
+  if ((q.st[p.par].done != 0) | (q.cg.stop >= 0)) return;
   const double beta = j > 0 ? q.cg.gamma[j & 1] / q.cg.gamma[(j - 1) & 1] : 0.0;
   pieces_finish(p, ncolp, 1, EpiCgStep<float>{p, q.cg.alpha, beta, j > 0 ? 1 : 0, (j + 1) & 1});
 }
@@ -267,12 +274,12 @@ __global__ __launch_bounds__(kBlock) void pc_step_finish_kernel(IterArgs<float> 
 // ---- building the pieces -----------------------------------------------------
 // Rows of the source are walked by one lane each, so a piece keeps the
 // source's order and nothing needs an atomic.
-__global__ __launch_bounds__(kBlock) void pc_count_kernel(Csr<float> A, SpPieces P) {
+__global__ __launch_bounds__(kBlock) void pc_count_kernel(Csr<float> A, SpPieces P, int *cnt) {
   const int r = blockIdx.x * kBlock + threadIdx.x;
   if (r >= A.rows) return;
   for (int s = 0; s < A.nseg; ++s) {
     const int *rp = A.rp + (size_t)s * A.rows + r;
-    for (int k = rp[0]; k < rp[1]; ++k) ++P.rp[(size_t)(A.ci[k] / P.seg) * P.rows + r];
+    for (int k = rp[0]; k < rp[1]; ++k) ++cnt[(size_t)(A.ci[k] / P.seg) * P.rows + r];
   }
 }
 
@@ -349,6 +356,21 @@ __global__ __launch_bounds__(kBlock) void pc_scan_kernel(int *v, int *copy, int6
   if (blockIdx.x == 0 && threadIdx.x == 0) v[len] = nnz;
 }
 
+// base and off from the rows' beginnings rp.
+__global__ __launch_bounds__(kBlock) void pc_bounds_kernel(const int *rp, SpPieces P, int nnz, unsigned *too_long) {
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x, per = (int64_t)P.blocks * 64;
+  if (i >= per * P.nseg) return;
+  const int *seg = rp + (i / per) * P.rows;
+  const int r = (int)(i % per), b0 = r & ~63, b1 = min(b0 + 64, P.rows);
+  const int len = seg[b1] - seg[b0];
+  P.off[i] = (uint16_t)(r < P.rows ? seg[r] - seg[b0] : len);
+  if (r == b0) {
+    P.base[i >> 6] = seg[b0];
+    if (len > 0xffff) *too_long = 1;
+  }
+  if (i == 0) P.base[(size_t)P.blocks * P.nseg] = nnz;
+}
+
 __global__ __launch_bounds__(kPcPad) void pc_pad_kernel(SpPieces P, int64_t nnz) {
   P.va[nnz + threadIdx.x] = 0.f;
   P.ci[nnz + threadIdx.x] = 0;
@@ -361,7 +383,7 @@ __global__ __launch_bounds__(kBlock) void pc_zero_kernel(int *v, int64_t len) {
 
 // Where the pieces are faster (CG step of the plain passes -> in pieces, us):
 //  - at least a million entries, so that the pass is bound by them:
-//    200000 x 50000, 6 a row: 31.6 -> 29.1; 2000000 x 200000, 16 a row: 500 -> 188;
+//    200000 x 50000, 6 a row: 31.6 -> 29.1; 2000000 x 200000, 16 a row: 500 -> 180;
 //  - at least 6 of a workgroup's 16 waves with rows of their own:
 //    100000 x 25000, 10 a row (7 and 12 waves): 31.1 -> 26.5;
 //    100000 x 10000, 20 a row (7 and 5): 40.7 -> 41.6;
@@ -375,8 +397,9 @@ bool pieces_shape(int64_t rows, int64_t cols, int64_t nnz, int groups, SpPieces 
   nseg = cdiv(cols, seg);
   const int64_t wgs = kPcWg / groups, rounds = cdiv(rows, wgs * kPcTile);
   if (nnz < ((int64_t)1 << 20) || rows < wgs * 64 * 6 || nnz < rows * nseg) return false;
-  if (rows >= (1LL << 30) || cols >= (1LL << 30) || rows * nseg >= (1LL << 31) - 1 || nnz >= (1LL << 31) - kPcPad - 1) return false;
+  if (rows >= (1LL << 30) || cols >= (1LL << 30) || (rows + 63) * nseg >= (1LL << 31) - 1 || nnz >= (1LL << 31) - kPcPad - 1) return false;
   P->rows = (int)rows;
+  P->blocks = (int)cdiv(rows, (int64_t)64);
   P->cols = (int)cols;
   P->seg = (int)seg;
   P->nseg = (int)nseg;
@@ -388,15 +411,18 @@ bool pieces_shape(int64_t rows, int64_t cols, int64_t nnz, int groups, SpPieces 
 
 int64_t pieces_sums(const SpPieces &P) { return cdiv((int64_t)P.rows * P.nseg, (int64_t)kScanBlock); }
 
-void fill_pieces(const Csr<float> &A, const SpPieces &P, int64_t nnz, int *cur, int *sums, hipStream_t s) {
+void fill_pieces(const Csr<float> &A, const SpPieces &P, int64_t nnz, int *rp, int *cur, int *sums,
+                 unsigned *too_long, hipStream_t s) {
   const int64_t len = (int64_t)P.rows * P.nseg, blocks = pieces_sums(P);
   const dim3 rows(cdiv(A.rows, kBlock)), b(kBlock);
-  hipLaunchKernelGGL(pc_zero_kernel, dim3(1024), b, 0, s, P.rp, len + 1);
-  hipLaunchKernelGGL(pc_count_kernel, rows, b, 0, s, A, P);
-  hipLaunchKernelGGL(pc_block_sums_kernel, dim3(blocks), b, 0, s, (const int *)P.rp, len, sums);
+  hipLaunchKernelGGL(pc_zero_kernel, dim3(1024), b, 0, s, rp, len + 1);
+  hipLaunchKernelGGL(pc_count_kernel, rows, b, 0, s, A, P, rp);
+  hipLaunchKernelGGL(pc_block_sums_kernel, dim3(blocks), b, 0, s, (const int *)rp, len, sums);
   hipLaunchKernelGGL(pc_scan_sums_kernel, dim3(1), b, 0, s, sums, blocks);
-  hipLaunchKernelGGL(pc_scan_kernel, dim3(blocks), b, 0, s, P.rp, cur, len, (const int *)sums, (int)nnz);
+  hipLaunchKernelGGL(pc_scan_kernel, dim3(blocks), b, 0, s, rp, cur, len, (const int *)sums, (int)nnz);
   hipLaunchKernelGGL(pc_scatter_kernel, rows, b, 0, s, A, P, cur);
+  hipLaunchKernelGGL(pc_bounds_kernel, dim3(cdiv((int64_t)P.blocks * 64 * P.nseg, (int64_t)kBlock)), b, 0, s,
+                     (const int *)rp, P, (int)nnz, too_long);
   hipLaunchKernelGGL(pc_pad_kernel, dim3(1), dim3(kPcPad), 0, s, P, nnz);
 }
 

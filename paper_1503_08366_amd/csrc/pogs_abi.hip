@@ -185,7 +185,7 @@ template <typename T> int alloc_iteration(pogs_ctx *c) {
   gemv_t_geometry(m, n, sizeof(T), &c->splits, &c->rps, &c->ncolp);
   c->nbx = (int)cdiv(n, kBlock);
   c->nby = (int)cdiv(m, kBlock);
-  const bool pieces = c->sp_pa.rp != nullptr;
+  const bool pieces = c->sp_pa.va != nullptr;
   c->n_pri = pieces ? c->sp_pa.tiles : c->sparse ? c->sp_grid : gemv_n_blocks(m, n, sizeof(T), 0);
   c->n_dual = pieces ? pieces_finish_blocks(n) : c->sparse ? c->sp_gridt : (int)cdiv(n, kFinishCols);
   if (c->sparse) c->splits = pieces ? c->sp_pat.groups : 1;  // partials of the column sums
@@ -451,31 +451,41 @@ void transpose_csr(const HostCsr &a, int n, int seg, HostCsr *t) {
 }
 
 void drop_pieces(pogs_ctx *c, SpPieces *p) {
-  c->arena.release(p->rp);
+  c->arena.release(p->base);
+  c->arena.release(p->off);
   c->arena.release(p->ci);
   c->arena.release(p->va);
   *p = SpPieces{};
 }
 
 // The copies in pieces where the shapes ask for them (a segment length given
-// by the caller is kept) and the memory is there.
+// by the caller is kept) and the memory is there.  Waits for the stream.
 int init_pieces(pogs_ctx *c, const Csr<float> &a, const Csr<float> &at, int64_t nnz) {
   SpPieces P[2];
   if (!pieces_shape(c->m, c->n, nnz, 1, &P[0]) || !pieces_shape(c->n, c->m, nnz, 8, &P[1])) return POGS_OK;
   DevArena tmp(c->stream);
-  int *cur[2], *sums[2];
-  for (int k = 0; k < 2; ++k) {
-    const size_t len = (size_t)P[k].rows * P[k].nseg;
-    if (c->arena.alloc((void **)&P[k].rp, (len + 1) * 4) ||
-        c->arena.alloc((void **)&P[k].ci, ((size_t)nnz + kPcPad) * 2) ||
-        c->arena.alloc((void **)&P[k].va, ((size_t)nnz + kPcPad) * 4) || tmp.alloc((void **)&cur[k], len * 4) ||
-        tmp.alloc((void **)&sums[k], (size_t)pieces_sums(P[k]) * 4)) {
-      for (SpPieces &q : P) drop_pieces(c, &q);
-      return POGS_OK;
-    }
+  int *rp[2], *cur[2], *sums[2];
+  unsigned *too_long, host = 0;
+  bool room = !tmp.alloc((void **)&too_long, sizeof(unsigned));
+  for (int k = 0; k < 2 && room; ++k) {
+    const size_t len = (size_t)P[k].rows * P[k].nseg, blocks = (size_t)P[k].blocks * P[k].nseg;
+    room = !c->arena.alloc((void **)&P[k].base, (blocks + 1) * 4) && !c->arena.alloc((void **)&P[k].off, blocks * 64 * 2) &&
+           !c->arena.alloc((void **)&P[k].ci, ((size_t)nnz + kPcPad) * 2) &&
+           !c->arena.alloc((void **)&P[k].va, ((size_t)nnz + kPcPad) * 4) &&
+           !tmp.alloc((void **)&rp[k], (len + 1) * 4) && !tmp.alloc((void **)&cur[k], len * 4) &&
+           !tmp.alloc((void **)&sums[k], (size_t)pieces_sums(P[k]) * 4);
   }
-  fill_pieces(a, P[0], nnz, cur[0], sums[0], c->stream);
-  fill_pieces(at, P[1], nnz, cur[1], sums[1], c->stream);
+  if (room) {
+    POGS_HIP_TRY(hipMemsetAsync(too_long, 0, sizeof(unsigned), c->stream));
+    fill_pieces(a, P[0], nnz, rp[0], cur[0], sums[0], too_long, c->stream);
+    fill_pieces(at, P[1], nnz, rp[1], cur[1], sums[1], too_long, c->stream);
+    POGS_HIP_TRY(hipMemcpyAsync(&host, too_long, sizeof(unsigned), hipMemcpyDeviceToHost, c->stream));
+    POGS_HIP_TRY(hipStreamSynchronize(c->stream));
+  }
+  if (!room || host) {
+    for (SpPieces &q : P) drop_pieces(c, &q);
+    return POGS_OK;
+  }
   c->sp_pa = P[0];
   c->sp_pat = P[1];
   return POGS_OK;
@@ -566,7 +576,7 @@ extern "C" int pogs_init_sparse(pogs_ctx **out, int64_t m, int64_t n, int64_t nn
   c->arena.stream = c->stream;
   rc = dt == POGS_F32 ? init_sparse_impl<float>(c, a, t) : init_sparse_impl<double>(c, a, t);
   if (!rc) rc = dt == POGS_F32 ? alloc_iteration<float>(c) : alloc_iteration<double>(c);
-  if (rc == POGS_ENOMEM && c->sp_pa.rp) {  // without them it may fit
+  if (rc == POGS_ENOMEM && c->sp_pa.va) {  // without them it may fit
     drop_pieces(c, &c->sp_pa);
     drop_pieces(c, &c->sp_pat);
     rc = alloc_iteration<float>(c);

@@ -346,7 +346,7 @@ template <typename T> static void launch_sp_step(const IterArgs<T> &p, int j, in
 template <typename T> void launch_iteration_cg_sparse(const IterArgs<T> &p, int cap, int ncolp, hipStream_t s) {
   launch_prox_cg<T>(p, s);
   if constexpr (sizeof(T) == 4) {
-    if (p.pa.rp) {
+    if (p.pa.va) {
       launch_pc_first(p, ncolp, s);
       for (int j = 0; j < cap; ++j) launch_pc_step(p, j, cap, ncolp, s);
       launch_pc_rows(p, cap, cap, s);
@@ -361,8 +361,8 @@ template <typename T> void launch_iteration_cg_sparse(const IterArgs<T> &p, int 
 template <typename T>
 void launch_iteration_cg_sparse_part(const IterArgs<T> &p, int which, int ncolp, hipStream_t s) {
   if constexpr (sizeof(T) == 4) {
-    if (p.pa.rp && which == 1) return launch_pc_first(p, ncolp, s);
-    if (p.pa.rp && which > 1) return launch_pc_step(p, 0, 1 << 30, ncolp, s);
+    if (p.pa.va && which == 1) return launch_pc_first(p, ncolp, s);
+    if (p.pa.va && which > 1) return launch_pc_step(p, 0, 1 << 30, ncolp, s);
   }
   if (which == 0) launch_prox_cg<T>(p, s);
   else if (which == 1) launch_sp_first<T>(p, s);

@@ -26,6 +26,9 @@ def _matrix(m, n, per_row, kind):
     cols = rng.integers(0, n, nnz)  # unsorted, some repeated within a row
     vals = rng.normal(size=nnz).astype(np.float32)
     A = sp.csr_matrix((vals, cols, ptr), shape=(m, n))
+    if kind == "full":  # 6 full columns side by side: more entries in 64 rows of A^T and one segment than 16 bits count
+        full = sp.csr_matrix(rng.normal(size=(m, 6)).astype(np.float32) * 0.1)
+        A = sp.hstack([full, A.tocsc()[:, 6:]], format="csr").astype(np.float32)
     if kind == "gaps":  # empty rows (whole groups of 64) and columns, a full column, a long row
         A = A.tocoo()
         keep = ~((A.row >= 640) & (A.row < 900)) & (A.col != 11) & (A.row != m - 1)
@@ -39,7 +42,7 @@ def _matrix(m, n, per_row, kind):
 
 
 @pytest.mark.parametrize("m,n,per_row,kind", [
-    (98304, 12288, 11, "plain"), (100003, 32129, 12, "plain"), (98305, 13001, 12, "gaps"),
+    (98304, 12288, 11, "plain"), (100003, 32129, 12, "plain"), (98305, 13001, 12, "gaps"), (98305, 13001, 12, "full"),
     (2100000, 12289, 1, "plain")])
 def test_pieces_match_plain_passes(m, n, per_row, kind):
     A = _matrix(m, n, per_row, kind)
