@@ -106,6 +106,7 @@ constexpr int kPcWaves = 16;                 // waves of a workgroup
 constexpr int kPcRpl = 8;                    // rows per lane at most
 constexpr int kPcTile = kPcWaves * 64 * kPcRpl;
 constexpr int kPcSeg = 32128;                // columns per segment at most
+constexpr int kPcGroups = 8;                 // workgroups that share a row range of A^T (one per XCD)
 constexpr int kPcPad = 256;                  // entries that may be read past the last
 struct SpPieces {
   int *base;

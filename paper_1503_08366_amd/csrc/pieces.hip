@@ -25,7 +25,7 @@
 //
 // A^ (more rows than columns): a workgroup goes through all segments and ends
 // with the rows' epilogue.  A^T: few long rows, so its segments are dealt to
-// kGroups workgroups per row range, whose float64 sums a finish kernel adds in
+// kPcGroups workgroups per row range, whose float64 sums a finish kernel adds in
 // order.  The column index inside a segment takes 16 bits: 6 bytes per entry
 // instead of 8.
 #include "cgls.hpp"
@@ -243,15 +243,22 @@ __global__ __launch_bounds__(kPcThreads) void pc_step_kernel(IterArgs<float> p, 
   pieces_cols_pass(p.pat, SrcVec{p.yt}, 0, p.part, ncolp, lds);
 }
 
-template <class Epi>
-__device__ __forceinline__ void pieces_finish(const IterArgs<float> &p, int ncolp, int nrhs, const Epi &e) {
+template <int NRHS, class Epi>
+__device__ __forceinline__ void pieces_finish(const IterArgs<float> &p, int ncolp, const Epi &e) {
   __shared__ double bs[kBlock / kWave];
   const int col = blockIdx.x * kBlock + threadIdx.x;
   Sum2 c{0.0, 0.0};
   if (col < p.n) {
-    double s[2] = {0.0, 0.0};
-    for (int r = 0; r < nrhs; ++r)
-      for (int g = 0; g < p.pat.groups; ++g) s[r] += p.part[(size_t)(r * p.pat.groups + g) * ncolp + col];
+    // every partial of the column loaded before the first is added
+    double v[NRHS][kPcGroups], s[2] = {0.0, 0.0};
+#pragma unroll
+    for (int r = 0; r < NRHS; ++r)
+#pragma unroll
+      for (int g = 0; g < kPcGroups; ++g) v[r][g] = p.part[(size_t)(r * kPcGroups + g) * ncolp + col];
+#pragma unroll
+    for (int r = 0; r < NRHS; ++r)
+#pragma unroll
+      for (int g = 0; g < kPcGroups; ++g) s[r] += v[r][g];
     c = e.column(col, s[0], s[1]);
   }
   const double a = block_sum(c.a, bs), b = block_sum(c.b, bs);
@@ -260,7 +267,7 @@ __device__ __forceinline__ void pieces_finish(const IterArgs<float> &p, int ncol
 
 __global__ __launch_bounds__(kBlock) void pc_first_finish_kernel(IterArgs<float> p, int ncolp) {
   if (!cg_first_enter<float>(p)) return;
-  pieces_finish(p, ncolp, 2, EpiCgFirst<float>{p});
+  pieces_finish<2>(p, ncolp, EpiCgFirst<float>{p});
 }
 
 // alpha_j is stored and in r1 already (the second sum is 0).
@@ -268,7 +275,7 @@ __global__ __launch_bounds__(kBlock) void pc_step_finish_kernel(IterArgs<float> 
   const Ctrl &q = *p.ctrl;
   if ((q.st[p.par].done != 0) | (q.cg.stop >= 0)) return;
   const double beta = j > 0 ? q.cg.gamma[j & 1] / q.cg.gamma[(j - 1) & 1] : 0.0;
-  pieces_finish(p, ncolp, 1, EpiCgStep<float>{p, q.cg.alpha, beta, j > 0 ? 1 : 0, (j + 1) & 1});
+  pieces_finish<1>(p, ncolp, EpiCgStep<float>{p, q.cg.alpha, beta, j > 0 ? 1 : 0, (j + 1) & 1});
 }
 
 // ---- building the pieces -----------------------------------------------------

@@ -462,7 +462,7 @@ void drop_pieces(pogs_ctx *c, SpPieces *p) {
 // by the caller is kept) and the memory is there.  Waits for the stream.
 int init_pieces(pogs_ctx *c, const Csr<float> &a, const Csr<float> &at, int64_t nnz) {
   SpPieces P[2];
-  if (!pieces_shape(c->m, c->n, nnz, 1, &P[0]) || !pieces_shape(c->n, c->m, nnz, 8, &P[1])) return POGS_OK;
+  if (!pieces_shape(c->m, c->n, nnz, 1, &P[0]) || !pieces_shape(c->n, c->m, nnz, kPcGroups, &P[1])) return POGS_OK;
   DevArena tmp(c->stream);
   int *rp[2], *cur[2], *sums[2];
   unsigned *too_long, host = 0;
