@@ -204,7 +204,7 @@ void launch_layout(const void *src, pogs_dtype sdt, pogs_order ord, int64_t lda,
 // (float64) and scales A in place to D A E.  ws: workspace (see setup.hip).
 template <typename T>
 int run_equilibrate(T *A, int m, int n, int ld, int iters, double eps_cmp, double *D, double *E,
-                    double *ws, size_t ws_bytes, unsigned *counters, hipStream_t s);
+                    double *ws, size_t ws_bytes, hipStream_t s);
 size_t equil_workspace_bytes(int m, int n);
 
 // Gram matrix of A^ (A^T A if m >= n else A A^T) plus I, as float64 q x q

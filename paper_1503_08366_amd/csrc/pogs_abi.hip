@@ -129,17 +129,13 @@ template <typename T> int init_impl(pogs_ctx *c, const void *A, pogs_dtype sdt, 
   // -- equilibration ------------------------------------------------------
   if ((rc = c->arena.alloc((void **)&c->D, (size_t)m * 8))) return rc;
   if ((rc = c->arena.alloc((void **)&c->E, (size_t)n * 8))) return rc;
-  unsigned *cnt;
-  const size_t ncnt = (size_t)cdiv(n, 128) + 16;
-  if ((rc = tmp.alloc((void **)&cnt, ncnt * sizeof(unsigned)))) return rc;
-  POGS_HIP_TRY(hipMemsetAsync(cnt, 0, ncnt * sizeof(unsigned), s));
   {
     const size_t wsb = equil_workspace_bytes(m, n);
     double *ws;
     if ((rc = tmp.alloc((void **)&ws, wsb))) return rc;
     double eps = c->params.eps_cmp > 0.0 ? c->params.eps_cmp
                                          : (sizeof(T) == 4 ? (double)FLT_EPSILON : DBL_EPSILON);
-    if ((rc = run_equilibrate<T>((T *)c->A, m, n, c->ld, c->params.equil_iters, eps, c->D, c->E, ws, wsb, cnt, s)))
+    if ((rc = run_equilibrate<T>((T *)c->A, m, n, c->ld, c->params.equil_iters, eps, c->D, c->E, ws, wsb, s)))
       return rc;
   }
   // -- Gram and factorisation (direct projection) -------------------------
@@ -208,12 +204,13 @@ template <typename T> int alloc_iteration(pogs_ctx *c) {
   // every per-context iteration buffer in one allocation
   Carve cv;
   const size_t o_vec = cv.take(c->vec_elems() * sizeof(T));
+  const size_t o_cnt = cv.take((size_t)(ntiles + 64) * sizeof(unsigned));
+  const size_t zero_bytes = cv.off;  // the vectors and the counters start at zero
   const size_t o_fh = cv.take(m), o_gh = cv.take(n);
   const size_t o_fs = cv.take((size_t)5 * m * sizeof(T)), o_gs = cv.take((size_t)5 * n * sizeof(T));
   const size_t o_raw = cv.take(c->fn_bytes);
   const size_t o_part = cv.take((size_t)std::max({c->splits, c->fp_blocks, c->cg_blocks}) * 2 * c->ncolp * 8);
   const size_t o_slots = cv.take((size_t)nslots * 8);
-  const size_t o_cnt = cv.take((size_t)(ntiles + 64) * sizeof(unsigned));
   const size_t o_ctrl = cv.take(sizeof(Ctrl));
   char *base;
   int rc;
@@ -232,8 +229,7 @@ template <typename T> int alloc_iteration(pogs_ctx *c) {
   c->slots = (double *)(base + o_slots);
   c->counters = (unsigned *)(base + o_cnt);
   c->ctrl = (Ctrl *)(base + o_ctrl);
-  POGS_HIP_TRY(hipMemsetAsync(c->vec, 0, c->vec_elems() * sizeof(T), c->stream));
-  POGS_HIP_TRY(hipMemsetAsync(c->counters, 0, (size_t)(ntiles + 64) * sizeof(unsigned), c->stream));
+  POGS_HIP_TRY(hipMemsetAsync(c->vec, 0, zero_bytes, c->stream));
   c->ctrl_host = (Ctrl *)pinned_slab().get();
   c->obj_host = (double *)pinned_slab().get();
   if (!c->ctrl_host || !c->obj_host) return POGS_ENOMEM;

@@ -88,8 +88,8 @@ bool equil_sweeps(const T *A, int m, int n, int ld, int iters, const EqArgs &a, 
   const int nsplit = (int)cdiv(m, rps);
   if ((size_t)nsplit * ncolp > part_doubles) return false;
   for (int it = 0; it < iters; ++it) {
-    hipLaunchKernelGGL((equil_sweep_kernel<T, U, R>), dim3(nsplit), dim3(kBlock), 0, s, A, m, n, ld, rps, a.e, a.d, part,
-                       ncolp, a.nf, a.gamma_m);
+    hipLaunchKernelGGL((equil_sweep_kernel<T, U, R>), dim3(nsplit), dim3(kBlock), 0, s, A, m, n, ld, rps,
+                       it ? (const double *)a.e : nullptr, a.d, part, ncolp, a.nf, a.gamma_m);
     hipLaunchKernelGGL((gemv_t_finish_kernel<1, EpiEqCol>), dim3(cdiv(n, kFinishCols)), dim3(kBlock), 0, s, n, nsplit,
                        (const double *)part, ncolp, EpiEqCol{a});
   }
@@ -138,7 +138,7 @@ size_t equil_workspace_bytes(int m, int n) {
 
 template <typename T>
 int run_equilibrate(T *A, int m, int n, int ld, int iters, double eps_cmp, double *D, double *E, double *ws,
-                    size_t ws_bytes, unsigned *counters, hipStream_t s) {
+                    size_t ws_bytes, hipStream_t s) {
   if (iters <= 0) {
     hipLaunchKernelGGL(fill_kernel, dim3(cdiv(m, 256)), dim3(256), 0, s, D, 1.0, m);
     hipLaunchKernelGGL(fill_kernel, dim3(cdiv(n, 256)), dim3(256), 0, s, E, 1.0, n);
@@ -159,9 +159,7 @@ int run_equilibrate(T *A, int m, int n, int ld, int iters, double eps_cmp, doubl
   a.gamma_n = gamma / n;
   a.mf = m;
   a.nf = n;
-  hipLaunchKernelGGL(fill_kernel, dim3(cdiv(n, 256)), dim3(256), 0, s, a.e, 1.0, n);
   const int tiles = (int)cdiv(n, gemv_t_tile(sizeof(T)));
-  (void)counters;
   const size_t part_doubles = ws_bytes / sizeof(double) - (size_t)(part - ws);
   // Sweeps of one pass over A where a workgroup holds a row's columns in
   // registers (6144 in float32, 3072 in float64), else two passes.  Whole setup
@@ -178,6 +176,7 @@ int run_equilibrate(T *A, int m, int n, int ld, int iters, double eps_cmp, doubl
   else if (U <= 6) room = equil_sweeps<T, 6, 2>(A, m, n, ld, iters, a, part, part_doubles, ncolp, s);
   else fused = false;
   if (!room) return POGS_ENOMEM;
+  if (!fused) hipLaunchKernelGGL(fill_kernel, dim3(cdiv(n, 256)), dim3(256), 0, s, a.e, 1.0, n);
   for (int it = 0; it < iters && !fused; ++it) {
     // rows: d = n / (|A|^2 e + gamma/m)
     {
@@ -418,10 +417,24 @@ int run_gram(const T *A, int m, int n, int ld, double *K, int Q, float *ws32, do
 // ---------------------------------------------------------------------------
 // Blocked Cholesky and explicit inverse (float64, 64 x 64 blocks)
 // ---------------------------------------------------------------------------
+// Workgroup 0 factors the first diagonal block (15 to 20 us, a chain); beside it the
+// others set B to I below row 64 (the block above is workgroup 0's) and K^{-1},
+// whose padding columns the row-dot kernels read, to zero.  In launches of their
+// own those two took 10 us of every setup.
+template <typename T>
 __global__ __launch_bounds__(256) void chol_first_kernel(const double *K, double *B, int Q, double *Dinv,
-                                                         unsigned *bad, unsigned *step) {
+                                                         unsigned *bad, unsigned *step, T *Kinv, size_t kinv_elems) {
   __shared__ CholLds cl;
-  chol_first_body(K, B, Q, Dinv, bad, step, cl);
+  if (blockIdx.x == 0) {
+    chol_first_body(K, B, Q, Dinv, bad, step, cl);
+    return;
+  }
+  const int b = blockIdx.x - 1;
+  trtri_init_rows(B, Q, NB + b * 8, min(Q, NB + b * 8 + 8));
+  using V = typename Vec16<T>::type;
+  const size_t pieces = kinv_elems / Vec16<T>::N;  // rows of a multiple of 64 elements
+  for (size_t i = (size_t)b * 256 + threadIdx.x; i < pieces; i += (size_t)(gridDim.x - 1) * 256)
+    reinterpret_cast<V *>(Kinv)[i] = V{};
 }
 
 // L_I0 = K_I0 X_00^T for I > 0 (the panel of step 0).
@@ -436,10 +449,6 @@ __global__ __launch_bounds__(256, 2) void chol_step_kernel(double *K, double *B,
   chol_step_body<T>(blockIdx.x, K, B, Q, nbt, kb, Dinv, q, Kinv, ldk, bad, step);
 }
 
-__global__ __launch_bounds__(256) void trtri_init_kernel(double *X, int Q) {
-  trtri_init_rows(X, Q, blockIdx.x * 8, min(Q, (int)blockIdx.x * 8 + 8));
-}
-
 size_t factor_workspace_bytes(int Q) { return ((size_t)Q * Q + (size_t)Q * NB) * sizeof(double); }
 
 // K (Q x Q, full symmetric I + G; overwritten) -> K^{-1} as T (q x q, row
@@ -451,11 +460,9 @@ int run_factor_inverse(double *K, int q, int Q, T *Kinv, int ldk, double *ws, un
   double *B = ws;
   double *Dinv = B + (size_t)Q * Q;
   unsigned *step = bad + 1;
-  hipLaunchKernelGGL(trtri_init_kernel, dim3(cdiv(Q, 8)), dim3(256), 0, s, B, Q);
-  hipLaunchKernelGGL(chol_first_kernel, dim3(1), dim3(256), 0, s, (const double *)K, B, Q, Dinv, bad, step);
+  hipLaunchKernelGGL(chol_first_kernel<T>, dim3(1 + std::max(1, (Q - NB) / 8)), dim3(256), 0, s, (const double *)K, B, Q,
+                     Dinv, bad, step, Kinv, (size_t)q * ldk);
   if (nbt > 1) hipLaunchKernelGGL(chol_panel0_kernel, dim3(nbt - 1), dim3(256), 0, s, K, Q, (const double *)Dinv);
-  // padding columns of K^{-1} are read (times zero) by the row-dot kernels: keep them zero
-  (void)hipMemsetAsync(Kinv, 0, (size_t)q * ldk * sizeof(T), s);
   const int nupd = nbt * (nbt + 1) / 2;
   for (int kb = 0; kb < nbt; ++kb)
     hipLaunchKernelGGL((chol_step_kernel<T>), dim3(nupd), dim3(256), 0, s, K, B, Q, nbt, kb, Dinv, q, Kinv, ldk, bad,
@@ -467,7 +474,7 @@ int run_factor_inverse(double *K, int q, int Q, T *Kinv, int ldk, double *ws, un
   template void launch_layout<T>(const void *, pogs_dtype, pogs_order, int64_t, int, int, T *, int,    \
                                  unsigned *, hipStream_t);                                             \
   template int run_equilibrate<T>(T *, int, int, int, int, double, double *, double *, double *,       \
-                                  size_t, unsigned *, hipStream_t);                                    \
+                                  size_t, hipStream_t);                                                \
   template int run_gram<T>(const T *, int, int, int, double *, int, float *, double *, size_t,         \
                            hipStream_t);                                                               \
   template int run_factor_inverse<T>(double *, int, int, T *, int, double *, unsigned *, hipStream_t);

@@ -104,7 +104,7 @@ __device__ __forceinline__ void equil_sweep_body(const Blk &b, const T *__restri
 #pragma unroll
     for (int k = 0; k < VN; ++k) {
       const int c = VN * t + CU * u + k;
-      ev[u][k] = c < n ? e[c] : 0.0;
+      ev[u][k] = c < n ? (e ? e[c] : 1.0) : 0.0;  // no e: the first sweep's ones
       col[u][k] = 0.0;
     }
   int g = 0;
