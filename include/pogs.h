@@ -158,7 +158,9 @@ typedef struct {
                             of its segmented copy (the passes over A^T gather
                             from one segment's piece of an m-vector at a time);
                             0 (default): 1 MB of the paired vector per segment,
-                            with at least two entries per row piece on average.
+                            with at least two entries per row piece on average;
+                            large float32 matrices then run on a further copy
+                            split to fit on-chip memory.
                             >= 0; results depend on it only through the
                             summation order. */
 } pogs_params;
