@@ -264,6 +264,32 @@ int pogs_solve(pogs_ctx *ctx, const pogs_fn *f, const pogs_fn *g, const pogs_par
 int pogs_solve_path(pogs_ctx *ctx, int32_t R, const pogs_fn *f, const pogs_fn *g,
                     const pogs_params *params, pogs_result *out);
 
+/* Residual-rule solves with the direct projection of matrices that fit the
+ * registers of the GPU (rows of up to 1024 entries on the shorter side, 20 to 40 MB)
+ * run a chunk of iterations in one launch whose workgroups, at most one per
+ * compute unit, exchange vectors through memory and so have to be on the GPU
+ * together.  Solves of one process take turns for that.  Where something else
+ * keeps the workgroups apart (long kernels on other streams, another
+ * process, a stream restricted to some compute units) they give up after a
+ * bounded wait, and the solve starts over with one launch per step.  The
+ * two ways agree up to rounding, not bit for bit, so a call can return other
+ * bits, and take longer, on a GPU that is shared like this. */
+
+/* How a context's solves run. */
+typedef struct {
+  int32_t resident_workgroups; /* workgroups of its resident launches; 0: it has none */
+  int32_t resident_last;       /* 1: the last pogs_solve ended on them */
+  int32_t resident_give_ups;   /* solves that gave up on them and started over */
+  int32_t sparse_pieces;       /* 1: sparse passes run on the copy split to fit
+                                  on-chip memory (see pogs_params.sparse_segment) */
+} pogs_route;
+int pogs_get_route(const pogs_ctx *ctx, pogs_route *out);
+
+/* Bound the wait of the context's resident workgroups: polls of about 0.7 us
+ * each (default 2^20); 0: they give up at their first wait; negative:
+ * the context's solves run one launch per step from the start. */
+int pogs_set_resident_wait(pogs_ctx *ctx, int32_t polls);
+
 /* Release a context and all its device memory.  NULL is a no-op. */
 int pogs_free(pogs_ctx *ctx);
 

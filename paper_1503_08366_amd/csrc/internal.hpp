@@ -338,10 +338,12 @@ ResGeom res_geometry(int64_t m, int64_t n, int elem_size);
 // Bytes of the exchange buffers (zero them before the first launch).
 size_t res_exchange_bytes(const ResGeom &r, int elem_size);
 struct ResHost;
-// One launch of `iters` iterations; first: of a solve.
+// One launch of `iters` iterations; first: of a solve; polls: the bound of a
+// workgroup's wait (default kResSpin).
+constexpr unsigned kResSpin = 1u << 20;
 template <typename T>
 int launch_resident(const IterArgs<T> &p, const ResGeom &r, const T *M, void *xbuf, ResHost *host, int first, int iters,
-                    hipStream_t s);
+                    unsigned polls, hipStream_t s);
 // Transpose of the scaled matrix (m x n, row stride ld) into n x m rows of stride ldt, padding zeroed.
 template <typename T> void launch_transpose(const T *A, int m, int n, int ld, T *At, int ldt, hipStream_t s);
 

@@ -783,7 +783,7 @@ template <typename T> int run_resident(pogs_ctx *c, int chunk, int verbose, bool
   int rc;
   const IterArgs<T> p = c->iter_args<T>();
   auto launch = [&](int first) {
-    return launch_resident<T>(p, c->res, c->res_matrix<T>(), c->res_x, h, first, chunk, s);
+    return launch_resident<T>(p, c->res, c->res_matrix<T>(), c->res_x, h, first, chunk, (unsigned)c->res_polls, s);
   };
   if ((rc = launch(1))) return rc;
   for (;;) {
@@ -800,7 +800,9 @@ template <typename T> int run_resident(pogs_ctx *c, int chunk, int verbose, bool
   POGS_HIP_TRY(hipStreamSynchronize(s));
   *failed = h->failed != 0;
   c->ctrl_host->st[0] = h->st;
-  c->res_epoch = *failed ? c->res_epoch + (1u << 20) : std::max(h->e1, h->e2) + 2;
+  // past every number used: a launch that gave up wrote none back, but used at
+  // most two an iteration
+  c->res_epoch = std::max({c->res_epoch, h->e1, h->e2}) + 2 + (*failed ? 2u * (unsigned)chunk + 2 : 0);
   return POGS_OK;
 }
 
@@ -857,12 +859,16 @@ template <typename T> int solve_impl(pogs_ctx *c, const pogs_fn *f, const pogs_f
     return POGS_OK;
   };
   bool stepwise = true;  // one launch per step of an iteration
-  if (c->res.G && cg_cap == 0 && !gap) {
+  if (c->res.G && c->res_polls >= 0 && cg_cap == 0 && !gap) {
     bool failed = false;
     if ((rc = start(false)) || (rc = run_resident<T>(c, chunk, p.verbose, &failed))) return rc;
     stepwise = failed;
-    if (failed) c->res = ResGeom{};  // the GPU is shared in a way that keeps the workgroups apart
+    if (failed) {  // the GPU is shared in a way that keeps the workgroups apart
+      ++c->res_give_ups;
+      if (p.verbose) fprintf(stderr, "pogs: resident workgroups gave up waiting; again with one launch per step\n");
+    }
   }
+  c->res_last = !stepwise;
   if (stepwise) {
     // tall float32 direct solves with the residual rule read A once per iteration
     if ((rc = start(c->fp_blocks > 0 && cg_cap == 0 && !gap)) || (rc = run_chunks<T>(c, p, chunk, cg_cap, gap))) return rc;
@@ -956,11 +962,12 @@ template <typename T> int profile_impl(pogs_ctx *c, int reps, double *ms) {
   const int launches = (int)cdiv(reps, chunk);
   const IterArgs<T> p = c->iter_args<T>();
   {
-    const bool resident = c->res.G && cg_cap == 0;  // as a solve runs them
+    const bool resident = c->res.G && c->res_polls >= 0 && cg_cap == 0;  // as a solve runs them
     std::unique_ptr<ResHold> hold(resident ? new ResHold(c->res.G) : nullptr);
     auto chunk_once = [&](int first) -> int {
       if (resident)
-        return launch_resident<T>(p, c->res, c->res_matrix<T>(), c->res_x, (ResHost *)c->flags_host, first, chunk, s);
+        return launch_resident<T>(p, c->res, c->res_matrix<T>(), c->res_x, (ResHost *)c->flags_host, first, chunk,
+                                  (unsigned)c->res_polls, s);
       POGS_HIP_TRY(hipGraphLaunch(c->graph, s));
       return POGS_OK;
     };
@@ -1015,6 +1022,21 @@ extern "C" int pogs_solve(pogs_ctx *ctx, const pogs_fn *f, const pogs_fn *g, con
   if (p.projection == POGS_PROJ_CGLS && p.stop_rule == POGS_STOP_GAP) return POGS_EUNSUPPORTED;
   return ctx->dt == POGS_F32 ? solve_impl<float>(ctx, f, g, p, x0, nu0, out)
                              : solve_impl<double>(ctx, f, g, p, x0, nu0, out);
+}
+
+extern "C" int pogs_get_route(const pogs_ctx *ctx, pogs_route *out) {
+  if (!ctx || !out) return POGS_EINVAL;
+  out->resident_workgroups = ctx->res.G;
+  out->resident_last = ctx->res_last;
+  out->resident_give_ups = ctx->res_give_ups;
+  out->sparse_pieces = ctx->sp_pa.va != nullptr;
+  return POGS_OK;
+}
+
+extern "C" int pogs_set_resident_wait(pogs_ctx *ctx, int32_t polls) {
+  if (!ctx) return POGS_EINVAL;
+  ctx->res_polls = polls;
+  return POGS_OK;
 }
 
 extern "C" int pogs_profile_iteration(pogs_ctx *ctx, int32_t reps, double *ms) {

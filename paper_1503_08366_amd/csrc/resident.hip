@@ -81,7 +81,7 @@ template <typename T, int NC, int RPW> static int launch_res(const ResArgs<T> &a
 
 template <typename T>
 int launch_resident(const IterArgs<T> &p, const ResGeom &r, const T *M, void *xbuf, ResHost *host, int first, int iters,
-                    hipStream_t s) {
+                    unsigned polls, hipStream_t s) {
   const bool wide = p.m < p.n;
   ResArgs<T> a{};
   a.L = wide ? p.n : p.m;
@@ -112,6 +112,7 @@ int launch_resident(const IterArgs<T> &p, const ResGeom &r, const T *M, void *xb
   a.x3 = a.x2 + res_words2<T>(r.G, r.nc);
   a.first = first;
   a.iters = iters;
+  a.polls = polls;
 #define POGS_RES_LAUNCH(NC, RPW) \
   if (r.pieces == NC && r.rpw == RPW) return launch_res<T, NC, RPW>(a, s);
   if constexpr (sizeof(T) == 4) {
@@ -140,7 +141,7 @@ template <typename T> void launch_transpose(const T *A, int m, int n, int ld, T 
 
 #define POGS_INST(T)                                                                                              \
   template int launch_resident<T>(const IterArgs<T> &, const ResGeom &, const T *, void *, ResHost *, int, int,   \
-                                  hipStream_t);                                                                   \
+                                  unsigned, hipStream_t);                                                         \
   template void launch_transpose<T>(const T *, int, int, int, T *, int, hipStream_t);
 POGS_INST(float)
 POGS_INST(double)

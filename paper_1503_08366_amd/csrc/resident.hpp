@@ -35,9 +35,9 @@
 // 3 of the iteration before (they published exchange 1 afterwards); exchange 1
 // itself alternates between two buffers, and is overwritten only after
 // another exchange 1 that needed every reader's words.
-// Every wait is bounded (kResSpin polls, about half a second): a workgroup that
-// gives up sets ctrl->res_failed and ends, the others run into the same bound,
-// and the host solves again with one launch per step.
+// Every wait is bounded (kResSpin polls, about 0.7 s): a workgroup that gives up
+// sets ctrl->res_failed and ends, the others run into the same bound, and the
+// host solves again with one launch per step.
 #pragma once
 
 #include "iter.hpp"
@@ -45,7 +45,6 @@
 namespace pogs {
 
 constexpr int kResThreads = 512;
-constexpr unsigned kResSpin = 1u << 20;
 typedef unsigned long long ResWord;
 
 // What the host reads after a launch (pinned memory).
@@ -65,6 +64,7 @@ template <typename T> struct ResArgs {
   ResHost *host;              // pinned: the state after the launch, for the host's check
   ResWord *x1[2], *x2, *x3;   // exchange buffers
   int first, iters;           // first launch of a solve; iterations per launch
+  unsigned polls;             // bound of a wait (0: every wait gives up at once)
 };
 
 // Words of the exchange buffers: 1 (each of two): per reader, writer and own
@@ -106,13 +106,17 @@ __device__ __forceinline__ ResWord res_get(const ResWord *p) {
 }
 
 // Words src(i), i < n, with the given tag into LDS dst(i).  Every thread loads
-// up to U words at once and tries again until all of them carry the tag.
+// up to U words at once and tries again until all of them carry the tag, at
+// most `polls` times.
 template <int U, class Src, class Dst>
-__device__ __forceinline__ void res_gather(int n, unsigned tag, int *bad, Src src, Dst dst) {
+__device__ __forceinline__ void res_gather(int n, unsigned tag, unsigned polls, int *bad, Src src, Dst dst) {
   for (int b = threadIdx.x; b < n; b += U * kResThreads) {
     ResWord x[U];
-    unsigned spin = 0;
-    for (;;) {
+    for (unsigned spin = 0;; ++spin) {
+      if (spin >= polls || ((spin & 1023) == 1023 && *(volatile int *)bad)) {
+        *(volatile int *)bad = 1;
+        break;
+      }
       unsigned miss = 0;
 #pragma unroll
       for (int u = 0; u < U; ++u)
@@ -121,10 +125,6 @@ __device__ __forceinline__ void res_gather(int n, unsigned tag, int *bad, Src sr
       for (int u = 0; u < U; ++u)
         if (b + u * kResThreads < n) miss |= (unsigned)(x[u] >> 32) ^ tag;
       if (!miss) break;
-      if (++spin > kResSpin || ((spin & 1023) == 0 && *(volatile int *)bad)) {
-        *(volatile int *)bad = 1;
-        break;
-      }
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -389,7 +389,7 @@ __device__ __forceinline__ void resident_body(const ResArgs<T> &p, char *smem) {
     {
       const ResWord *own = p.x1[e1 & 1] + (size_t)g * n1, *tail = p.x1[e1 & 1] + (size_t)G * n1 - n1;
       unsigned *r32 = (unsigned *)red, *s32 = (unsigned *)sums - n1;
-      res_gather<8>((int)n1 + 4 * G, e1, &bad, [&](int i) { return (i < (int)n1 ? own : tail) + i; },
+      res_gather<8>((int)n1 + 4 * G, e1, p.polls, &bad, [&](int i) { return (i < (int)n1 ? own : tail) + i; },
                     [&](int i) { return (i < (int)n1 ? r32 : s32) + i; });
     }
     __syncthreads();
@@ -461,7 +461,7 @@ __device__ __forceinline__ void resident_body(const ResArgs<T> &p, char *smem) {
     {
       const float inv_ch = 1.0f / (float)ch;
       unsigned *vr = (unsigned *)vecr, *v1 = (unsigned *)vec1, *s32 = (unsigned *)sums;
-      res_gather<8>(G * ch, e2, &bad, [&](int i) { return p.x2 + i; },
+      res_gather<8>(G * ch, e2, p.polls, &bad, [&](int i) { return p.x2 + i; },
                     [&](int i) {
                       const int o = (int)(((float)i + 0.5f) * inv_ch), k = i - o * ch;
                       const int e = o * nw + (k < nw ? k : k - nw);  // word of the vector
@@ -499,7 +499,7 @@ __device__ __forceinline__ void resident_body(const ResArgs<T> &p, char *smem) {
     }
     {
       unsigned *v0 = (unsigned *)vec0;
-      res_gather<4>(q * W, e2, &bad, [&](int i) { return p.x3 + i; }, [&](int i) { return v0 + i; });
+      res_gather<4>(q * W, e2, p.polls, &bad, [&](int i) { return p.x3 + i; }, [&](int i) { return v0 + i; });
     }
     __syncthreads();
     if (bad) return fail();

@@ -66,6 +66,11 @@ class pogs_result(C.Structure):
                 ("error", C.c_int32), ("gap", C.c_double), ("eps_gap", C.c_double)]
 
 
+class pogs_route(C.Structure):
+    _fields_ = [("resident_workgroups", C.c_int32), ("resident_last", C.c_int32),
+                ("resident_give_ups", C.c_int32), ("sparse_pieces", C.c_int32)]
+
+
 class pogs_problem(C.Structure):
     _fields_ = [("m", C.c_int64), ("n", C.c_int64), ("A", C.c_void_p), ("dt", C.c_int),
                 ("ord", C.c_int), ("lda", C.c_int64), ("f", pogs_fn), ("g", pogs_fn),
@@ -92,6 +97,8 @@ _SIGS = {
                              C.c_void_p, C.c_void_p, C.POINTER(pogs_result)]),
     "pogs_solve_path": (C.c_int, [C.c_void_p, C.c_int32, C.POINTER(pogs_fn), C.POINTER(pogs_fn),
                                   C.POINTER(pogs_params), C.POINTER(pogs_result)]),
+    "pogs_get_route": (C.c_int, [C.c_void_p, C.POINTER(pogs_route)]),
+    "pogs_set_resident_wait": (C.c_int, [C.c_void_p, C.c_int32]),
     "pogs_free": (C.c_int, [C.c_void_p]),
     "pogs_get_scaling": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int]),
     "pogs_project": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int]),
@@ -473,6 +480,17 @@ class Context:
             out.append(r)
             prev = r
         return out
+
+    def route(self) -> pogs_route:
+        """How the context's solves run (pogs_get_route)."""
+        r = pogs_route()
+        _check(_lib().pogs_get_route(self._h(), C.byref(r)), "pogs_get_route")
+        return r
+
+    def set_resident_wait(self, polls: int):
+        """Bound the wait of resident workgroups (pogs_set_resident_wait);
+        negative: one launch per step."""
+        _check(_lib().pogs_set_resident_wait(self._h(), polls), "pogs_set_resident_wait")
 
     def profile_iteration(self, reps: int = 50):
         """Average ms of a full iteration and of each part of it (HIP events):
