@@ -285,9 +285,11 @@ typedef struct {
 } pogs_route;
 int pogs_get_route(const pogs_ctx *ctx, pogs_route *out);
 
-/* Bound the wait of the context's resident workgroups: polls of about 0.7 us
- * each (default 2^20); 0: they give up at their first wait; negative:
- * the context's solves run one launch per step from the start. */
+/* Bound the wait of the context's resident workgroups for each other at the
+ * start of a launch: polls of about 0.5 us each (default POGS_RESIDENT_WAIT);
+ * 0: they give up at once; negative: the context's solves run one
+ * launch per step from the start. */
+#define POGS_RESIDENT_WAIT 16384
 int pogs_set_resident_wait(pogs_ctx *ctx, int32_t polls);
 
 /* Release a context and all its device memory.  NULL is a no-op. */

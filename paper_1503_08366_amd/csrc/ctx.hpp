@@ -341,7 +341,7 @@ struct pogs_ctx {
   ResGeom res;
   void *res_x = nullptr, *At = nullptr;
   unsigned res_epoch = 0;
-  int res_polls = (int)kResSpin;  // bound of a resident workgroup's wait; < 0: one launch per step
+  int res_polls = (int)kResArrive;  // bound of a resident workgroup's wait; < 0: one launch per step
   int res_last = 0, res_give_ups = 0;  // the last solve ended on resident launches; solves that started over
   bool res_wanted = true;  // false: the contexts of the batch call and the serving engine (see init_context)
 

@@ -339,8 +339,8 @@ ResGeom res_geometry(int64_t m, int64_t n, int elem_size);
 size_t res_exchange_bytes(const ResGeom &r, int elem_size);
 struct ResHost;
 // One launch of `iters` iterations; first: of a solve; polls: the bound of a
-// workgroup's wait (default kResSpin).
-constexpr unsigned kResSpin = 1u << 20;
+// workgroup's wait for all others to arrive (kResSpin: its later waits).
+constexpr unsigned kResArrive = POGS_RESIDENT_WAIT, kResSpin = 1u << 20;
 template <typename T>
 int launch_resident(const IterArgs<T> &p, const ResGeom &r, const T *M, void *xbuf, ResHost *host, int first, int iters,
                     unsigned polls, hipStream_t s);

@@ -35,9 +35,15 @@
 // 3 of the iteration before (they published exchange 1 afterwards); exchange 1
 // itself alternates between two buffers, and is overwritten only after
 // another exchange 1 that needed every reader's words.
-// Every wait is bounded (kResSpin polls, about 0.7 s): a workgroup that gives up
-// sets ctrl->res_failed and ends, the others run into the same bound, and the
-// host solves again with one launch per step.
+// Every wait is bounded.  Until a workgroup has seen words of this launch from
+// all others, some may not be on the GPU yet: other streams' kernels hold their
+// CUs, or will not leave any.  It waits kResArrive polls (about 7 ms) for them.
+// Under a stream of 0.9 ms kernels a 1.2 ms solve takes 4.6 ms so, where one launch
+// per step took 109; behind 120 ms kernels, or with half the CUs masked off, the
+// wait is lost, and with a bound of kResSpin (0.7 s, now the bound once all have
+// arrived) such a solve took 570 and 766 ms.  A workgroup that gives up sets
+// ctrl->res_failed and ends; the others, and those that start later, see that
+// and end too, and the host solves again with one launch per step.
 #pragma once
 
 #include "iter.hpp"
@@ -64,7 +70,7 @@ template <typename T> struct ResArgs {
   ResHost *host;              // pinned: the state after the launch, for the host's check
   ResWord *x1[2], *x2, *x3;   // exchange buffers
   int first, iters;           // first launch of a solve; iterations per launch
-  unsigned polls;             // bound of a wait (0: every wait gives up at once)
+  unsigned polls;             // bound of a wait until all workgroups have arrived (0: it gives up before its first wait)
 };
 
 // Words of the exchange buffers: 1 (each of two): per reader, writer and own
@@ -105,18 +111,21 @@ __device__ __forceinline__ ResWord res_get(const ResWord *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// ctrl->res_failed, set and seen while a launch runs.
+__device__ __forceinline__ int res_gave_up(const Ctrl *c) {
+  return __hip_atomic_load(&c->res_failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Words src(i), i < n, with the given tag into LDS dst(i).  Every thread loads
 // up to U words at once and tries again until all of them carry the tag, at
-// most `polls` times.
+// most `polls` times and not after another workgroup has given up.
 template <int U, class Src, class Dst>
-__device__ __forceinline__ void res_gather(int n, unsigned tag, unsigned polls, int *bad, Src src, Dst dst) {
+__device__ __forceinline__ void res_gather(int n, unsigned tag, unsigned polls, const Ctrl *ctrl, int *bad, Src src,
+                                           Dst dst) {
   for (int b = threadIdx.x; b < n; b += U * kResThreads) {
     ResWord x[U];
-    for (unsigned spin = 0;; ++spin) {
-      if (spin >= polls || ((spin & 1023) == 1023 && *(volatile int *)bad)) {
-        *(volatile int *)bad = 1;
-        break;
-      }
+    unsigned spin = 0;
+    for (;;) {
       unsigned miss = 0;
 #pragma unroll
       for (int u = 0; u < U; ++u)
@@ -125,6 +134,10 @@ __device__ __forceinline__ void res_gather(int n, unsigned tag, unsigned polls, 
       for (int u = 0; u < U; ++u)
         if (b + u * kResThreads < n) miss |= (unsigned)(x[u] >> 32) ^ tag;
       if (!miss) break;
+      if (++spin > polls || ((spin & 63) == 0 && (*(volatile int *)bad || res_gave_up(ctrl)))) {
+        *(volatile int *)bad = 1;
+        break;
+      }
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -190,11 +203,11 @@ __device__ __forceinline__ void resident_body(const ResArgs<T> &p, char *smem) {
   if (t == 0) bad = 0;
   auto fail = [&]() {
     if (t == 0) {
-      p.ctrl->res_failed = 1;
+      __hip_atomic_store(&p.ctrl->res_failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       p.host->failed = 1;
     }
   };
-  if (p.ctrl->res_failed) return fail();
+  if (p.polls == 0 || res_gave_up(p.ctrl)) return fail();
   if (st.done) return;
   const CtrlParams qc = ctrl_params(p.ctrl);
   const double eps_abs = qc.eps_abs, eps_rel = qc.eps_rel;
@@ -301,6 +314,7 @@ __device__ __forceinline__ void resident_body(const ResArgs<T> &p, char *smem) {
   double rho = st.rho, resc = st.rescale;  // of the half step to form
   double res2 = 0.0, lnorm2 = 0.0, r_s = 0.0, eps_s = 0.0, eps_l = 0.0;
   int it = 0;
+  unsigned polls = p.polls;
   for (;;) {
     // float32 rows stay float32 in their registers: without this the compiler
     // widens them all ahead of the loop, twice the registers
@@ -389,7 +403,7 @@ __device__ __forceinline__ void resident_body(const ResArgs<T> &p, char *smem) {
     {
       const ResWord *own = p.x1[e1 & 1] + (size_t)g * n1, *tail = p.x1[e1 & 1] + (size_t)G * n1 - n1;
       unsigned *r32 = (unsigned *)red, *s32 = (unsigned *)sums - n1;
-      res_gather<8>((int)n1 + 4 * G, e1, p.polls, &bad, [&](int i) { return (i < (int)n1 ? own : tail) + i; },
+      res_gather<8>((int)n1 + 4 * G, e1, polls, p.ctrl, &bad, [&](int i) { return (i < (int)n1 ? own : tail) + i; },
                     [&](int i) { return (i < (int)n1 ? r32 : s32) + i; });
     }
     __syncthreads();
@@ -461,7 +475,7 @@ __device__ __forceinline__ void resident_body(const ResArgs<T> &p, char *smem) {
     {
       const float inv_ch = 1.0f / (float)ch;
       unsigned *vr = (unsigned *)vecr, *v1 = (unsigned *)vec1, *s32 = (unsigned *)sums;
-      res_gather<8>(G * ch, e2, p.polls, &bad, [&](int i) { return p.x2 + i; },
+      res_gather<8>(G * ch, e2, polls, p.ctrl, &bad, [&](int i) { return p.x2 + i; },
                     [&](int i) {
                       const int o = (int)(((float)i + 0.5f) * inv_ch), k = i - o * ch;
                       const int e = o * nw + (k < nw ? k : k - nw);  // word of the vector
@@ -472,6 +486,7 @@ __device__ __forceinline__ void resident_body(const ResArgs<T> &p, char *smem) {
     }
     __syncthreads();
     if (bad) return fail();
+    polls = kResSpin;  // every workgroup is here
     // ---- solve ----------------------------------------------------------------------
     sum_pairs(2);
     double x0, x1;
@@ -499,7 +514,7 @@ __device__ __forceinline__ void resident_body(const ResArgs<T> &p, char *smem) {
     }
     {
       unsigned *v0 = (unsigned *)vec0;
-      res_gather<4>(q * W, e2, p.polls, &bad, [&](int i) { return p.x3 + i; }, [&](int i) { return v0 + i; });
+      res_gather<4>(q * W, e2, polls, p.ctrl, &bad, [&](int i) { return p.x3 + i; }, [&](int i) { return v0 + i; });
     }
     __syncthreads();
     if (bad) return fail();

@@ -25,6 +25,7 @@ POGS_OK, POGS_EINVAL, POGS_ENOMEM, POGS_EDEVICE, POGS_EAGAIN, POGS_ENOTFOUND, PO
     0, -1, -2, -3, -4, -5, -6
 POGS_ETOOBIG = -7
 POGS_NOALLOC_SCRATCH_BYTES = 64 << 20
+POGS_RESIDENT_WAIT = 16384
 POGS_CONVERGED, POGS_MAXITER, POGS_NUMERICAL, POGS_CANCELLED, POGS_FAILED = 0, 1, 2, 3, 4
 POGS_F32, POGS_F64 = 0, 1
 POGS_ROW_MAJOR, POGS_COL_MAJOR = 0, 1
