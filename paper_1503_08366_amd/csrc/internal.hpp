@@ -334,6 +334,7 @@ struct ResGeom {
 };
 // Workgroups of resident solves that fit the device together (its CUs).
 int res_capacity();
+bool res_all_cus(hipStream_t s);  // the stream runs on all of them
 ResGeom res_geometry(int64_t m, int64_t n, int elem_size);
 // Bytes of the exchange buffers (zero them before the first launch).
 size_t res_exchange_bytes(const ResGeom &r, int elem_size);

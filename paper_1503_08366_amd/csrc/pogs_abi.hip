@@ -806,6 +806,13 @@ template <typename T> int run_resident(pogs_ctx *c, int chunk, int verbose, bool
   return POGS_OK;
 }
 
+// Whether the next residual-rule solve goes to resident launches.  A wait other
+// than the default is the caller's word that it shall.
+bool resident_now(const pogs_ctx *c) {
+  if (!c->res.G || c->res_polls < 0) return false;
+  return c->res_polls != (int)kResArrive || res_all_cus(c->stream);
+}
+
 template <typename T> int solve_impl(pogs_ctx *c, const pogs_fn *f, const pogs_fn *g, const pogs_params &p,
                                      const void *x0, const void *nu0, pogs_result *out) {
   const double t0 = now_ms();
@@ -859,7 +866,7 @@ template <typename T> int solve_impl(pogs_ctx *c, const pogs_fn *f, const pogs_f
     return POGS_OK;
   };
   bool stepwise = true;  // one launch per step of an iteration
-  if (c->res.G && c->res_polls >= 0 && cg_cap == 0 && !gap) {
+  if (cg_cap == 0 && !gap && resident_now(c)) {
     bool failed = false;
     if ((rc = start(false)) || (rc = run_resident<T>(c, chunk, p.verbose, &failed))) return rc;
     stepwise = failed;
@@ -962,7 +969,7 @@ template <typename T> int profile_impl(pogs_ctx *c, int reps, double *ms) {
   const int launches = (int)cdiv(reps, chunk);
   const IterArgs<T> p = c->iter_args<T>();
   {
-    const bool resident = c->res.G && c->res_polls >= 0 && cg_cap == 0;  // as a solve runs them
+    const bool resident = cg_cap == 0 && resident_now(c);  // as a solve runs them
     std::unique_ptr<ResHold> hold(resident ? new ResHold(c->res.G) : nullptr);
     auto chunk_once = [&](int first) -> int {
       if (resident)

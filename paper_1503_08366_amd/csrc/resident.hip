@@ -30,6 +30,20 @@ int res_capacity() {
   return std::min(n, 256);
 }
 
+// Streams restricted to some CUs never run resident launches: two of them can
+// overlap, so what fits together is not known, and waiting it out takes 7 ms of
+// a 2 ms solve (8000 x 1000 on half the CUs: 9.0 ms, with one launch per step 2.1).
+bool res_all_cus(hipStream_t s) {
+  uint32_t mask[32] = {};
+  if (hipExtStreamGetCUMask(s, 32, mask) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  int n = 0;
+  for (uint32_t w : mask) n += __builtin_popcount(w);
+  return n >= res_capacity();
+}
+
 // Shapes taken: those whose rows fit the registers of the CUs (rows of up to
 // 1024 entries; 20 MB of matrix at half the CUs, 40 MB at all of them).  Of the
 // kernels for a row length the first that needs at most 128 workgroups, else the

@@ -53,3 +53,16 @@ def test_workgroups_kept_apart_give_up_soon():
             assert (ctx.route().resident_last, ctx.route().resident_give_ups) == (0, i)
             for k in ("x", "y", "mu", "nu"):
                 np.testing.assert_array_equal(getattr(r, k), getattr(want, k))
+
+
+@pytest.mark.parametrize("units,resident", [(256, 1), (255, 0), (128, 0)])
+def test_restricted_stream_runs_one_launch_per_step(units, resident):
+    """A context on a stream that leaves out compute units does not wait for
+    workgroups at all; a mask of all units is no restriction."""
+    p = _problem()
+    with _masked_stream(units) as s:
+        for _ in range(2):  # contexts made one after another: nothing is learned from the first
+            with P.Context(p.A, stream=s) as ctx:
+                assert ctx.solve(p.f, p.g).converged
+                r = ctx.route()
+                assert (r.resident_workgroups, r.resident_last, r.resident_give_ups) == (200, resident, 0)
