@@ -265,15 +265,17 @@ int pogs_solve_path(pogs_ctx *ctx, int32_t R, const pogs_fn *f, const pogs_fn *g
                     const pogs_params *params, pogs_result *out);
 
 /* Residual-rule solves with the direct projection of matrices that fit the
- * registers of the GPU (rows of up to 1024 entries on the shorter side, 20 to 40 MB)
- * run a chunk of iterations in one launch whose workgroups, at most one per
- * compute unit, exchange vectors through memory and so have to be on the GPU
- * together.  Solves of one process take turns for that.  A context on a stream
- * restricted to some compute units runs one launch per step instead.  Where
- * something else keeps the workgroups apart (long kernels on other streams,
- * another process) they give up after a bounded wait, and the solve starts over
- * with one launch per step.  The two ways agree up to rounding, not bit for bit, so a call can
- * return other bits, and take longer, on a GPU that is shared like this. */
+ * registers of the GPU (rows of up to 1024 entries on the shorter side, 20 to
+ * 40 MB) run a chunk of iterations in one launch whose workgroups, at most one
+ * per compute unit, exchange vectors through memory and so have to be on the
+ * GPU together.  Solves of one process take turns for that.  A context on a
+ * stream restricted to some compute units runs one launch per step instead.
+ * Where something else keeps the workgroups apart (long kernels on other
+ * streams, another process) they give up after a bounded wait, the solve
+ * starts over with one launch per step, and no context of the process tries
+ * on that GPU for the next 0.1 s (up to 3.2 s after several in a row).  The
+ * two ways agree up to rounding, not bit for bit, so a call can return other
+ * bits, and take longer, on a GPU that is shared like this. */
 
 /* How a context's solves run. */
 typedef struct {
@@ -289,7 +291,7 @@ int pogs_get_route(const pogs_ctx *ctx, pogs_route *out);
  * start of a launch: polls of about 0.5 us each (default POGS_RESIDENT_WAIT);
  * 0: they give up at once; negative: the context's solves run one
  * launch per step from the start.  Another bound than the default also makes
- * a context on a restricted stream try. */
+ * a context on a restricted stream, or after another's give-up, try. */
 #define POGS_RESIDENT_WAIT 16384
 int pogs_set_resident_wait(pogs_ctx *ctx, int32_t polls);
 

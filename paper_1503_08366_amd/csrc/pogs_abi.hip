@@ -734,8 +734,22 @@ template <typename T> int run_chunks(pogs_ctx *c, const pogs_params &p, int chun
 // solve needs all of its workgroups on the GPU together, so the sum stays
 // within the CU count (one workgroup per CU always fits; other kernels end by
 // themselves).  First come, first served.
+// Also what is known of others on that GPU: after a solve gave up waiting, no
+// context tries for kPause, twice as long each time in a row up to kPauseMost;
+// a solve that got through ends that.  At 7 ms a try that is a few hundredths
+// of the time of a program that shares the GPU for good.
 class ResSlots {
  public:
+  static constexpr double kPause = 100.0, kPauseMost = 3200.0;  // ms
+  bool try_now() {
+    std::lock_guard<std::mutex> lk(mu_);
+    return now_ms() >= retry_at_;
+  }
+  void outcome(bool gave_up) {
+    std::lock_guard<std::mutex> lk(mu_);
+    pause_ = gave_up ? std::min(std::max(2.0 * pause_, kPause), kPauseMost) : 0.0;
+    retry_at_ = now_ms() + pause_;
+  }
   void acquire(int g) {
     std::unique_lock<std::mutex> lk(mu_);
     const unsigned long long mine = tail_++;
@@ -761,6 +775,7 @@ class ResSlots {
   std::condition_variable cv_;
   int used_ = 0;
   unsigned long long head_ = 0, tail_ = 0;
+  double pause_ = 0.0, retry_at_ = 0.0;
 };
 struct ResHold {
   ResSlots &s;
@@ -799,6 +814,7 @@ template <typename T> int run_resident(pogs_ctx *c, int chunk, int verbose, bool
   }
   POGS_HIP_TRY(hipStreamSynchronize(s));
   *failed = h->failed != 0;
+  if (res_all_cus(s)) hold.s.outcome(*failed);  // a restricted stream says nothing about others
   c->ctrl_host->st[0] = h->st;
   // past every number used: a launch that gave up wrote none back, but used at
   // most two an iteration
@@ -810,7 +826,7 @@ template <typename T> int run_resident(pogs_ctx *c, int chunk, int verbose, bool
 // than the default is the caller's word that it shall.
 bool resident_now(const pogs_ctx *c) {
   if (!c->res.G || c->res_polls < 0) return false;
-  return c->res_polls != (int)kResArrive || res_all_cus(c->stream);
+  return c->res_polls != (int)kResArrive || (ResSlots::of_device().try_now() && res_all_cus(c->stream));
 }
 
 template <typename T> int solve_impl(pogs_ctx *c, const pogs_fn *f, const pogs_fn *g, const pogs_params &p,

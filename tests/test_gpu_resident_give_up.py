@@ -20,6 +20,18 @@ KEYS = ("x", "y", "mu", "nu")
 DEFAULT_POLLS = 1 << 20
 
 
+@pytest.fixture(autouse=True)
+def _no_pause_left():
+    """A give-up keeps contexts from trying for a while; a solve with a bound of
+    its own that gets through ends that."""
+    yield
+    p = W.lasso(64, 32, seed=1)
+    with P.Context(p.A) as ctx:
+        ctx.set_resident_wait(DEFAULT_POLLS)
+        ctx.solve(p.f, p.g)
+        assert ctx.route().resident_last == 1
+
+
 def _bits(a, b):
     assert a.iters == b.iters and a.status == b.status
     for k in KEYS:
