@@ -281,7 +281,7 @@ int pogs_solve_path(pogs_ctx *ctx, int32_t R, const pogs_fn *f, const pogs_fn *g
 typedef struct {
   int32_t resident_workgroups; /* workgroups of its resident launches; 0: it has none */
   int32_t resident_last;       /* 1: the last pogs_solve ended on them */
-  int32_t resident_give_ups;   /* solves that gave up on them and started over */
+  int32_t resident_give_ups;   /* solves (and profiles) that gave up on them and started over */
   int32_t sparse_pieces;       /* 1: sparse passes run on the copy split to fit
                                   on-chip memory (see pogs_params.sparse_segment) */
 } pogs_route;
@@ -342,7 +342,7 @@ int pogs_prox_noalloc(const pogs_fn *fn, pogs_dtype dt, double rho, const void *
  * disabled it runs `reps` full iterations as captured launch sequences, then
  * `reps` back-to-back launches of each iteration kernel alone, and writes
  *   ms[0] average ms per full iteration (in the launches a residual-rule solve
- *   on the context uses),
+ *   on the context uses; one launch per step after resident ones gave up),
  *   direct projection: ms[1] prox step, ms[2] first pass over A, ms[3] solve
  *   with the cached inverse, ms[4] second pass over A; when m >= n the prox
  *   step runs inside the first pass and its finish (ms[1] = 0, ms[2] covers

@@ -974,7 +974,6 @@ template <typename T> int profile_impl(pogs_ctx *c, int reps, double *ms) {
   h.cg.stop = -1;
   h.res_e1 = h.res_e2 = c->res_epoch;
   *c->ctrl_host = h;
-  POGS_HIP_TRY(hipMemcpyAsync(c->ctrl, c->ctrl_host, sizeof(Ctrl), hipMemcpyHostToDevice, s));
   const int chunk = even_chunk(c->params.chunk_iters);
   int rc;
   if ((rc = ensure_graph<T>(c, chunk, cg_cap, 0))) return rc;
@@ -984,25 +983,38 @@ template <typename T> int profile_impl(pogs_ctx *c, int reps, double *ms) {
   float t = 0.f;
   const int launches = (int)cdiv(reps, chunk);
   const IterArgs<T> p = c->iter_args<T>();
-  {
-    const bool resident = cg_cap == 0 && resident_now(c);  // as a solve runs them
-    std::unique_ptr<ResHold> hold(resident ? new ResHold(c->res.G) : nullptr);
-    auto chunk_once = [&](int first) -> int {
-      if (resident)
-        return launch_resident<T>(p, c->res, c->res_matrix<T>(), c->res_x, (ResHost *)c->flags_host, first, chunk,
-                                  (unsigned)c->res_polls, s);
-      POGS_HIP_TRY(hipGraphLaunch(c->graph, s));
-      return POGS_OK;
-    };
-    if ((rc = chunk_once(1))) return rc;  // warm
+  auto time_chunks = [&](const auto &launch) -> int {
+    int e;
+    POGS_HIP_TRY(hipMemcpyAsync(c->ctrl, c->ctrl_host, sizeof(Ctrl), hipMemcpyHostToDevice, s));
+    if ((e = launch(1))) return e;  // warm
     POGS_HIP_TRY(hipEventRecord(e0, s));
     for (int i = 0; i < launches; ++i)
-      if ((rc = chunk_once(0))) return rc;
+      if ((e = launch(0))) return e;
     POGS_HIP_TRY(hipEventRecord(e1, s));
     POGS_HIP_TRY(hipEventSynchronize(e1));
     POGS_HIP_TRY(hipEventElapsedTime(&t, e0, e1));
-    if (resident) c->res_epoch += (1u << 20) + 2u * (unsigned)chunk * (unsigned)(launches + 1);
+    return POGS_OK;
+  };
+  bool stepwise = true;
+  if (cg_cap == 0 && resident_now(c)) {  // as a solve runs them
+    ResHost *host = (ResHost *)c->flags_host;
+    *host = ResHost{};
+    ResHold hold(c->res.G);
+    if ((rc = time_chunks([&](int first) {
+           return launch_resident<T>(p, c->res, c->res_matrix<T>(), c->res_x, host, first, chunk,
+                                     (unsigned)c->res_polls, s);
+         })))
+      return rc;
+    c->res_epoch += 2u * (unsigned)chunk * (unsigned)(launches + 1) + 4;
+    stepwise = host->failed != 0;  // gave up: the time is that of the wait
+    if (res_all_cus(s)) hold.s.outcome(stepwise);
+    c->res_give_ups += stepwise;
   }
+  if (stepwise && (rc = time_chunks([&](int) -> int {
+        POGS_HIP_TRY(hipGraphLaunch(c->graph, s));
+        return POGS_OK;
+      })))
+    return rc;
   ms[0] = (double)t / ((double)launches * chunk);
   auto part = [&](int w) {
     if (c->sparse) launch_iteration_cg_sparse_part<T>(p, w, c->ncolp, s);

@@ -103,3 +103,22 @@ def test_rejects_null():
     lib = P.load()
     assert lib.pogs_get_route(None, C.byref(P.pogs_route())) == P.POGS_EINVAL
     assert lib.pogs_set_resident_wait(None, 0) == P.POGS_EINVAL
+
+
+@pytest.mark.parametrize("m,n,dt", [(8000, 1000, np.float32), (300, 900, np.float64)])
+def test_profile_after_a_give_up_times_launches_per_step(m, n, dt):
+    """A profile whose resident launches gave up reports the iteration that ran
+    instead: five launches, none under 2 us, and not the launches that returned."""
+    p = W.lasso(m, n, seed=9, dtype=dt)
+    with P.Context(p.A) as ctx:
+        want = ctx.solve(p.f, p.g)
+        ctx.set_resident_wait(-1)
+        steps = min(ctx.profile_iteration(100)["iteration"] for _ in range(3))
+        ctx.set_resident_wait(0)
+        given_up = min(ctx.profile_iteration(100)["iteration"] for _ in range(3))
+        assert ctx.route().resident_give_ups == 3
+        assert given_up > 0.01 and 0.7 * steps < given_up < 1.4 * steps
+        ctx.set_resident_wait(DEFAULT_POLLS)
+        assert ctx.profile_iteration(100)["iteration"] < 0.9 * steps
+        _bits(ctx.solve(p.f, p.g), want)
+        assert ctx.route().resident_last == 1 and ctx.route().resident_give_ups == 3
