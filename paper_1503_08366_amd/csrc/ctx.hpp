@@ -144,9 +144,10 @@ struct DevArena {
   static constexpr uint64_t kPoolKeep = 16ull << 30;
 };
 
-// Small pinned host blocks (control-block read-backs), carved from pinned
-// pages that live until the process ends: pinning costs far more than a
-// small solve's host work.
+// Small pinned host blocks (control-block read-backs, objectives and resident
+// solves' states that kernels write), carved from pinned pages that live until
+// the process ends: pinning costs far more than a small solve's host work.
+// Contexts of every device share them.
 class PinnedSlab {
  public:
   static constexpr size_t kChunk = 1024, kPage = 64 * 1024;
@@ -154,7 +155,7 @@ class PinnedSlab {
     std::lock_guard<std::mutex> lk(mu_);
     if (free_.empty()) {
       void *pg = nullptr;
-      if (hipHostMalloc(&pg, kPage) != hipSuccess) return nullptr;
+      if (hipHostMalloc(&pg, kPage, hipHostMallocPortable) != hipSuccess) return nullptr;
       for (size_t i = 0; i < kPage / kChunk; ++i) free_.push_back((char *)pg + i * kChunk);
     }
     void *p = free_.back();
