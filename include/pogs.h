@@ -159,10 +159,18 @@ typedef struct {
                             from one segment's piece of an m-vector at a time);
                             0 (default): 1 MB of the paired vector per segment,
                             with at least two entries per row piece on average;
-                            large float32 matrices then run on a further copy
-                            split to fit on-chip memory.
-                            >= 0; results depend on it only through the
-                            summation order. */
+                            large float32 matrices (from 2^20 entries, 98304
+                            rows and 12288 columns) whose rows and columns are
+                            short and alike enough then run on a further copy
+                            split to fit on-chip memory (see pogs_route), 6 bytes
+                            per entry for each of A and A^T and 2 per row and
+                            segment beside the plain copies, where memory
+                            allows; there r1 - alpha q is rounded to float32
+                            before A^T is applied, so results agree with those
+                            of the plain copies within float32 rounding of the
+                            CG state.  > 0: always the plain copies, and results
+                            depend on its value only through the summation
+                            order. */
 } pogs_params;
 
 /* Result of a solve: the half-step tuple (x, y, mu, nu) of the last iteration,

@@ -303,15 +303,25 @@ template <typename T>
 void run_equilibrate_sparse(Csr<T> A, Csr<T> At, int m, int n, int iters, double eps_cmp, double *D, double *E,
                             double *ws, hipStream_t s);
 // The copies in pieces (pieces.hip).  pieces_shape: false where the row
-// passes over the plain copy are used instead.  fill_pieces: the arrays of P
-// from the scaled A; rp holds nseg rows + 1 int, cur nseg rows int, sums
-// pieces_sums(P) int; *too_long is set where the entries of 64 rows in one
-// segment exceed 16 bits (the pieces are then not to be used).
+// passes over the plain copy are used instead, by the matrix's size.
+// count_pieces: base and off of P from the scaled A, and *st (zeroed by the
+// caller); rp holds nseg rows + 1 int, cur nseg rows int, sums pieces_sums(P)
+// int, cost nseg blocks float.  pieces_pay: by the rows' lengths, from both
+// matrices' stats and the lanes per row of the plain passes.  fill_pieces: the rest
+// of P (cur as count_pieces left it).
 // launch_pc_*: the passes of a projection (start, one CG step, its rows alone).
 bool pieces_shape(int64_t rows, int64_t cols, int64_t nnz, int groups, SpPieces *P);
 int64_t pieces_sums(const SpPieces &P);
-void fill_pieces(const Csr<float> &A, const SpPieces &P, int64_t nnz, int *rp, int *cur, int *sums,
-                 unsigned *too_long, hipStream_t s);
+struct PcStats {
+  unsigned too_long;  // the entries of 64 rows in one segment exceed 16 bits: no pieces
+  float worst_ns;     // estimate of a pass's longest workgroup
+  int longest;        // entries of the longest row (0: none is longer than a lane's walk)
+  int pad;
+};
+void count_pieces(const Csr<float> &A, const SpPieces &P, int64_t nnz, int *rp, int *cur, int *sums, float *cost,
+                  PcStats *st, hipStream_t s);
+bool pieces_pay(const PcStats &a, const PcStats &at, int lpr, int lprt, int64_t nnz);
+void fill_pieces(const Csr<float> &A, const SpPieces &P, int64_t nnz, int *cur, hipStream_t s);
 int pieces_finish_blocks(int n);
 void launch_pc_first(const IterArgs<float> &p, int ncolp, hipStream_t s);
 void launch_pc_rows(const IterArgs<float> &p, int j, int cap, hipStream_t s);

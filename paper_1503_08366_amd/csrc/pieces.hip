@@ -309,7 +309,8 @@ template <class F> __device__ __forceinline__ void pc_segments(const SpPieces &P
   }
 }
 
-__global__ __launch_bounds__(kPcCountThreads) void pc_count_kernel(Csr<float> A, SpPieces P, int *cnt) {
+// Also the longest row (rows of up to kPcLongRow entries count as none).
+__global__ __launch_bounds__(kPcCountThreads) void pc_count_kernel(Csr<float> A, SpPieces P, int *cnt, PcStats *st) {
   constexpr int NW = kPcCountThreads / 64;
   __shared__ unsigned long long longs[NW];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -319,6 +320,7 @@ __global__ __launch_bounds__(kPcCountThreads) void pc_count_kernel(Csr<float> A,
     pc_row(A, r, [&](int k0, int k1) {
       for (int k = k0; k < k1; ++k) ++cnt[(size_t)(A.ci[k] / P.seg) * P.rows + r];
     });
+  if (len > kPcLongRow) atomicMax(&st->longest, len);
   const unsigned long long mine = __ballot(len > kPcLongRow);
   if (lane == 0) longs[w] = mine;
   __syncthreads();
@@ -447,7 +449,7 @@ __global__ __launch_bounds__(kBlock) void pc_scan_kernel(int *v, int *copy, int6
 }
 
 // base and off from the rows' beginnings rp.
-__global__ __launch_bounds__(kBlock) void pc_bounds_kernel(const int *rp, SpPieces P, int nnz, unsigned *too_long) {
+__global__ __launch_bounds__(kBlock) void pc_bounds_kernel(const int *rp, SpPieces P, int nnz, PcStats *st) {
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x, per = (int64_t)P.blocks * 64;
   if (i >= per * P.nseg) return;
   const int *seg = rp + (i / per) * P.rows;
@@ -456,9 +458,49 @@ __global__ __launch_bounds__(kBlock) void pc_bounds_kernel(const int *rp, SpPiec
   P.off[i] = (uint16_t)(r < P.rows ? seg[r] - seg[b0] : len);
   if (r == b0) {
     P.base[i >> 6] = seg[b0];
-    if (len > 0xffff) *too_long = 1;
+    if (len > 0xffff) st->too_long = 1;
   }
   if (i == 0) P.base[(size_t)P.blocks * P.nseg] = nnz;
+}
+
+// What a wave does with 64 rows of a segment takes the longest row's share of each
+// chunk, added up by one lane (kPcAddNs an entry, in fours), and the chunks after the
+// first, whose loads are waited for (kPcChunkNs each).  cost[seg blocks + b]: that sum.
+constexpr float kPcAddNs = 45.f, kPcChunkNs = 1100.f;
+__global__ __launch_bounds__(kBlock) void pc_cost_kernel(SpPieces P, float *cost) {
+  const int lane = threadIdx.x & 63;
+  const int64_t i = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
+  if (i >= (int64_t)P.blocks * P.nseg) return;
+  const int begin = P.base[i], ke = P.base[i + 1], lo = P.off[i * 64 + lane];
+  const int next = __shfl_down(lo, 1), from = begin + lo, hi = lane == 63 ? ke : begin + next;
+  int adds = 0, chunks = 0;
+  for (int k = begin & ~3; k < ke; k += kPcChunk, ++chunks) {
+    int run = max(0, min(hi - k, kPcChunk) - max(from - k, 0));
+    for (int o = 32; o > 0; o >>= 1) run = max(run, __shfl_xor(run, o));
+    adds += (run + 3) & ~3;
+  }
+  if (lane == 0) cost[i] = kPcAddNs * (float)adds + kPcChunkNs * (float)max(chunks - 1, 0);
+}
+
+// The longest workgroup: a barrier per segment, each wave its blocks of the tile.
+__global__ __launch_bounds__(64) void pc_worst_kernel(SpPieces P, const float *cost, PcStats *st) {
+  const int grp = blockIdx.x % P.groups, tile = blockIdx.x / P.groups, w = threadIdx.x & 15, g0 = threadIdx.x >> 4;
+  const int per = (P.nseg + P.groups - 1) / P.groups;
+  const int sg0 = min(P.nseg, grp * per), sg1 = min(P.nseg, sg0 + per);
+  const int r0 = tile * P.tile, r1 = min(P.rows, r0 + P.tile);
+  float t = 0.f;
+  for (int sg = sg0; sg < sg1; ++sg) {
+    float v = 0.f;
+    for (int g = g0; g < kPcRpl; g += 4) {
+      const int row = r0 + (g * kPcWaves + w) * 64;
+      if (row < r1) v += cost[(size_t)sg * P.blocks + (row >> 6)];
+    }
+    v += __shfl_xor(v, 16);
+    v += __shfl_xor(v, 32);
+    for (int o = 8; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
+    t += v;
+  }
+  if (threadIdx.x == 0) atomicMax((unsigned *)&st->worst_ns, __float_as_uint(t));  // not negative: ordered as its bits
 }
 
 __global__ __launch_bounds__(kPcPad) void pc_pad_kernel(SpPieces P, int64_t nnz) {
@@ -479,7 +521,8 @@ __global__ __launch_bounds__(kBlock) void pc_zero_kernel(int *v, int64_t len) {
 //    100000 x 10000, 20 a row (7 and 5): 40.7 -> 41.6;
 //  - at least one entry per row and segment, or the row bounds outweigh them:
 //    500000 x 125000, 9 a row (2.3): 84.7 -> 49.7;
-//    1000000 x 250000, 6 a row (0.75): 95.7 -> 94.9 and the first pass 103 -> 125.
+//    1000000 x 250000, 6 a row (0.75): 95.7 -> 94.9 and the first pass 103 -> 125;
+// and where pieces_pay says so.
 bool pieces_shape(int64_t rows, int64_t cols, int64_t nnz, int groups, SpPieces *P) {
   *P = SpPieces{};
   int64_t nseg = round_up(cdiv(cols, (int64_t)kPcSeg), groups);
@@ -499,20 +542,50 @@ bool pieces_shape(int64_t rows, int64_t cols, int64_t nnz, int groups, SpPieces 
   return true;
 }
 
+// A row belongs to one lane, so dense rows, long rows and rows of unlike lengths
+// side by side leave most lanes of a wave, or most workgroups, without work: the
+// pass takes what its longest workgroup takes (pc_cost_kernel, from the matrix's own
+// bounds), or its entries' loads.  The plain passes give a row lpr lanes and
+// deal rows out evenly; they take their entries' gathers, or the longest row's
+// chain of them (an estimate that is low where many rows are long).  CG steps, us, plain /
+// pieces -> chosen:
+//    200000 x 20000, 24 entries a row 68 / 50, 48: 121 / 117, 100: 272 / 368, 200: 502 / 1202
+//      -> pieces up to 48;
+//    1000000 x 20000, 32 a row 463 / 299, 64: 893 / 867 with 1000 / 1428 for the
+//      first pass (A^T twice) -> pieces at 32: A^T counts 1.2 times;
+//    column frequencies 1 / (rank + 100), frequent ones side by side, 300000 x 30000
+//      105 / 1976, 2000000 x 200000 2253 / 12006 -> plain; the same columns
+//      in random order 120 / 125 and 2400 / 736 -> pieces for the larger;
+//    rows sorted by length 1 / (rank + 1000), 2000000 x 200000: 730 / 26996 -> plain;
+//    a full column, 300000 x 30000 (64 lanes a row) 2150 / 1731 -> plain, 500000 x
+//      125000 11545 / 2868, 2000000 x 200000 56100 / 11730 (16 lanes) -> pieces.
+bool pieces_pay(const PcStats &a, const PcStats &at, int lpr, int lprt, int64_t nnz) {
+  if (a.too_long || at.too_long) return false;
+  constexpr double kLoadNs = 0.0025, kGatherNs = 0.007, kChainNs = 440.0;  // per entry, entry, turn of a row's lanes
+  auto pieces = [&](const PcStats &s) { return std::max(kLoadNs * (double)nnz, (double)s.worst_ns); };
+  auto plain = [&](const PcStats &s, int l) { return std::max(kGatherNs * (double)nnz, kChainNs * (double)s.longest / l); };
+  return pieces(a) + 1.2 * pieces(at) < plain(a, lpr) + plain(at, lprt);
+}
+
 int64_t pieces_sums(const SpPieces &P) { return cdiv((int64_t)P.rows * P.nseg, (int64_t)kScanBlock); }
 
-void fill_pieces(const Csr<float> &A, const SpPieces &P, int64_t nnz, int *rp, int *cur, int *sums,
-                 unsigned *too_long, hipStream_t s) {
+void count_pieces(const Csr<float> &A, const SpPieces &P, int64_t nnz, int *rp, int *cur, int *sums, float *cost,
+                  PcStats *st, hipStream_t s) {
   const int64_t len = (int64_t)P.rows * P.nseg, blocks = pieces_sums(P);
-  const dim3 rows(cdiv(A.rows, kBlock)), b(kBlock);
+  const dim3 b(kBlock);
   hipLaunchKernelGGL(pc_zero_kernel, dim3(1024), b, 0, s, rp, len + 1);
-  hipLaunchKernelGGL(pc_count_kernel, dim3(cdiv(A.rows, kPcCountThreads)), dim3(kPcCountThreads), 0, s, A, P, rp);
+  hipLaunchKernelGGL(pc_count_kernel, dim3(cdiv(A.rows, kPcCountThreads)), dim3(kPcCountThreads), 0, s, A, P, rp, st);
   hipLaunchKernelGGL(pc_block_sums_kernel, dim3(blocks), b, 0, s, (const int *)rp, len, sums);
   hipLaunchKernelGGL(pc_scan_sums_kernel, dim3(1), b, 0, s, sums, blocks);
   hipLaunchKernelGGL(pc_scan_kernel, dim3(blocks), b, 0, s, rp, cur, len, (const int *)sums, (int)nnz);
-  hipLaunchKernelGGL(pc_scatter_kernel, rows, b, 0, s, A, P, cur);
-  hipLaunchKernelGGL(pc_bounds_kernel, dim3(cdiv((int64_t)P.blocks * 64 * P.nseg, (int64_t)kBlock)), b, 0, s,
-                     (const int *)rp, P, (int)nnz, too_long);
+  const dim3 per_row(cdiv((int64_t)P.blocks * 64 * P.nseg, (int64_t)kBlock));
+  hipLaunchKernelGGL(pc_bounds_kernel, per_row, b, 0, s, (const int *)rp, P, (int)nnz, st);
+  hipLaunchKernelGGL(pc_cost_kernel, per_row, b, 0, s, P, cost);
+  hipLaunchKernelGGL(pc_worst_kernel, dim3(P.tiles * P.groups), dim3(64), 0, s, P, (const float *)cost, st);
+}
+
+void fill_pieces(const Csr<float> &A, const SpPieces &P, int64_t nnz, int *cur, hipStream_t s) {
+  hipLaunchKernelGGL(pc_scatter_kernel, dim3(cdiv(A.rows, kBlock)), dim3(kBlock), 0, s, A, P, cur);
   hipLaunchKernelGGL(pc_pad_kernel, dim3(1), dim3(kPcPad), 0, s, P, nnz);
 }
 

@@ -454,34 +454,38 @@ void drop_pieces(pogs_ctx *c, SpPieces *p) {
   *p = SpPieces{};
 }
 
-// The copies in pieces where the shapes ask for them (a segment length given
-// by the caller is kept) and the memory is there.  Waits for the stream.
+// The copies in pieces where they are faster (a segment length given by the
+// caller is kept) and the memory is there.  Waits for the stream.
 int init_pieces(pogs_ctx *c, const Csr<float> &a, const Csr<float> &at, int64_t nnz) {
   SpPieces P[2];
   if (!pieces_shape(c->m, c->n, nnz, 1, &P[0]) || !pieces_shape(c->n, c->m, nnz, kPcGroups, &P[1])) return POGS_OK;
   DevArena tmp(c->stream);
+  const Csr<float> *src[2] = {&a, &at};
   int *rp[2], *cur[2], *sums[2];
-  unsigned *too_long, host = 0;
-  bool room = !tmp.alloc((void **)&too_long, sizeof(unsigned));
-  for (int k = 0; k < 2 && room; ++k) {
+  float *cost[2];
+  PcStats *st, host[2];
+  bool take = !tmp.alloc((void **)&st, sizeof(host));
+  for (int k = 0; k < 2 && take; ++k) {
     const size_t len = (size_t)P[k].rows * P[k].nseg, blocks = (size_t)P[k].blocks * P[k].nseg;
-    room = !c->arena.alloc((void **)&P[k].base, (blocks + 1) * 4) && !c->arena.alloc((void **)&P[k].off, blocks * 64 * 2) &&
-           !c->arena.alloc((void **)&P[k].ci, ((size_t)nnz + kPcPad) * 2) &&
-           !c->arena.alloc((void **)&P[k].va, ((size_t)nnz + kPcPad) * 4) &&
+    take = !c->arena.alloc((void **)&P[k].base, (blocks + 1) * 4) && !c->arena.alloc((void **)&P[k].off, blocks * 64 * 2) &&
            !tmp.alloc((void **)&rp[k], (len + 1) * 4) && !tmp.alloc((void **)&cur[k], len * 4) &&
-           !tmp.alloc((void **)&sums[k], (size_t)pieces_sums(P[k]) * 4);
+           !tmp.alloc((void **)&sums[k], (size_t)pieces_sums(P[k]) * 4) && !tmp.alloc((void **)&cost[k], blocks * 4);
   }
-  if (room) {
-    POGS_HIP_TRY(hipMemsetAsync(too_long, 0, sizeof(unsigned), c->stream));
-    fill_pieces(a, P[0], nnz, rp[0], cur[0], sums[0], too_long, c->stream);
-    fill_pieces(at, P[1], nnz, rp[1], cur[1], sums[1], too_long, c->stream);
-    POGS_HIP_TRY(hipMemcpyAsync(&host, too_long, sizeof(unsigned), hipMemcpyDeviceToHost, c->stream));
+  if (take) {
+    POGS_HIP_TRY(hipMemsetAsync(st, 0, sizeof(host), c->stream));
+    for (int k = 0; k < 2; ++k) count_pieces(*src[k], P[k], nnz, rp[k], cur[k], sums[k], cost[k], st + k, c->stream);
+    POGS_HIP_TRY(hipMemcpyAsync(host, st, sizeof(host), hipMemcpyDeviceToHost, c->stream));
     POGS_HIP_TRY(hipStreamSynchronize(c->stream));
+    take = pieces_pay(host[0], host[1], a.lpr, at.lpr, nnz);
   }
-  if (!room || host) {
+  for (int k = 0; k < 2 && take; ++k)
+    take = !c->arena.alloc((void **)&P[k].ci, ((size_t)nnz + kPcPad) * 2) &&
+           !c->arena.alloc((void **)&P[k].va, ((size_t)nnz + kPcPad) * 4);
+  if (!take) {
     for (SpPieces &q : P) drop_pieces(c, &q);
     return POGS_OK;
   }
+  for (int k = 0; k < 2; ++k) fill_pieces(*src[k], P[k], nnz, cur[k], c->stream);
   c->sp_pa = P[0];
   c->sp_pat = P[1];
   return POGS_OK;
