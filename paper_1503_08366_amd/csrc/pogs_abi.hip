@@ -737,7 +737,14 @@ template <typename T> int run_chunks(pogs_ctx *c, const pogs_params &p, int chun
 // Workgroups of resident solves on one GPU at once, over all threads: each
 // solve needs all of its workgroups on the GPU together, so the sum stays
 // within the CU count (one workgroup per CU always fits; other kernels end by
-// themselves).  First come, first served.
+// themselves).  First come, first served, a whole solve at a time, or a launch at
+// a time while more solves are about than the process has hardware queues: two
+// whose streams share a queue run their launches one after the other, and as
+// holders of all slots they did so to their ends.  us a solve with whole
+// solves / launches at a time / one launch per step: 8 threads 1000 x 1000
+// 958 / 896 / 842, 3000 x 700 float64 638 / 564 / 712, 1999 x 503 679 / 423 / 1717; 12 threads
+// 1096 / 949 / 840, 624 / 586 / 711, 642 / 452 / 1718; with 4 threads 800 / 831 / 866 and
+// 498 / 490 / 726.
 // Also what is known of others on that GPU: after a solve gave up waiting, no
 // context tries for kPause, twice as long each time in a row up to kPauseMost;
 // a solve that got through ends that.  At 7 ms a try that is a few hundredths
@@ -759,13 +766,19 @@ class ResSlots {
     const unsigned long long mine = tail_++;
     cv_.wait(lk, [&] { return mine == head_ && (used_ == 0 || used_ + g <= res_capacity()); });
     used_ += g;
+    ++holders_;
     ++head_;
     cv_.notify_all();
   }
   void release(int g) {
     std::lock_guard<std::mutex> lk(mu_);
     used_ -= g;
+    --holders_;
     cv_.notify_all();
+  }
+  bool crowded() {
+    std::lock_guard<std::mutex> lk(mu_);
+    return head_ != tail_ && holders_ + (int)(tail_ - head_) > kHwQueues;
   }
   static ResSlots &of_device() {
     static ResSlots s[64];
@@ -777,7 +790,8 @@ class ResSlots {
  private:
   std::mutex mu_;
   std::condition_variable cv_;
-  int used_ = 0;
+  static constexpr int kHwQueues = 4;  // HIP's default
+  int used_ = 0, holders_ = 0;
   unsigned long long head_ = 0, tail_ = 0;
   double pause_ = 0.0, retry_at_ = 0.0;
 };
@@ -790,7 +804,7 @@ struct ResHold {
 
 // The iterations of a solve as resident launches of `chunk` iterations, each
 // queued while the host waits for the one before (after the launch that stops,
-// the next one returns at once).  *failed: a workgroup gave up waiting; the
+// the next one returns at once), unless solves take turns.  *failed: a workgroup gave up waiting; the
 // state is then meaningless.
 template <typename T> int run_resident(pogs_ctx *c, int chunk, int verbose, bool *failed) {
   hipStream_t s = c->stream;
@@ -807,7 +821,8 @@ template <typename T> int run_resident(pogs_ctx *c, int chunk, int verbose, bool
   if ((rc = launch(1))) return rc;
   for (;;) {
     POGS_HIP_TRY(hipEventRecord(done, s));
-    if ((rc = launch(0))) return rc;
+    const bool turns = hold.s.crowded();
+    if (!turns && (rc = launch(0))) return rc;
     POGS_HIP_TRY(hipEventSynchronize(done));
     const CtrlState cs = h->st;
     if (verbose)
@@ -815,6 +830,11 @@ template <typename T> int run_resident(pogs_ctx *c, int chunk, int verbose, bool
               cs.eps_pri, cs.r_dual, cs.eps_dual, cs.rho);
     *failed = *(volatile int *)&h->failed != 0;
     if (*failed || cs.done) break;
+    if (turns) {
+      hold.s.release(hold.g);
+      hold.s.acquire(hold.g);
+      if ((rc = launch(0))) return rc;
+    }
   }
   POGS_HIP_TRY(hipStreamSynchronize(s));
   *failed = h->failed != 0;
