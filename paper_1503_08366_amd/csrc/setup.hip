@@ -79,9 +79,12 @@ template <typename T, int U, int R>
 bool equil_sweeps(const T *A, int m, int n, int ld, int iters, const EqArgs &a, double *part, size_t part_doubles,
                   int ncolp, hipStream_t s) {
   // fewer where a workgroup's rows are worth more than its share of the partial
-  // sums that the finish adds (float64 3000 x 700, whole setup without a factor:
-  // 207 us with 750, 185 with 375; float32 1000 x 5000: 290 with 500, 246 with 250)
-  const int most = std::is_same<T, double>::value ? 512 : U <= 4 ? 1024 : 256;
+  // sums that the finish adds.  Whole setups without a factor, us, at 256 / 512 / 1024:
+  // float64 3000 x 700 172 / 176 / 197, 20000 x 1000 542 / 473 / 498, 10000 x 500 - / 233 / 237,
+  // 40000 x 512 - / 529 / 501, 200000 x 400 - / 2443 / 2043; float32 1000 x 5000 238 / 284 / 283,
+  // 4000 x 6000 412 / 445 / 444, 12000 x 5000 741 / 713 / 712, 30000 x 4200 1735 / 1504 / 1499
+  // (the last two lose to the small ones' cap; two passes take 1046 and 2263)
+  const int most = std::is_same<T, double>::value ? (U == 1 && m > 16384 ? 1024 : 512) : U <= 4 ? 1024 : 256;
   const int nwg = (int)std::min<int64_t>(
       std::min(most, resident_workgroups((const void *)equil_sweep_kernel<T, U, R>, kBlock)), cdiv(m, R));
   const int rps = (int)round_up(cdiv(m, nwg), R);
@@ -165,11 +168,16 @@ int run_equilibrate(T *A, int m, int n, int ld, int iters, double eps_cmp, doubl
   // registers (6144 in float32, 3072 in float64), else two passes.  Whole setup
   // without a factor, two passes -> one: float64 200 x 100 197 -> 164 us,
   // 4000 x 2000 428 -> 283, 20000 x 1000 681 -> 477; float32 12000 x 5000
-  // 1061 -> 759.
+  // 1061 -> 759.  A row takes a barrier of a whole workgroup, so rows that fill
+  // few of its lanes keep to two passes in float64 unless there are too few of
+  // them for that to matter (two passes / one: 4000 x 192 171 / 158, 10000 x 192 196 / 205,
+  // 150000 x 192 935 / 1010, 150000 x 256 1325 / 1183, 80000 x 100 401 / 566, 1000000 x 64
+  // 2292 / 5322).
   constexpr int CU = kBlock * Vec16<T>::N;
   const int U = (int)cdiv(n, CU);
-  bool fused = true, room = true;
-  if (U == 1) room = equil_sweeps<T, 1, 4>(A, m, n, ld, iters, a, part, part_doubles, ncolp, s);
+  bool fused = !(std::is_same<T, double>::value && n < 224 && m > 6144), room = true;
+  if (!fused) {}
+  else if (U == 1) room = equil_sweeps<T, 1, 4>(A, m, n, ld, iters, a, part, part_doubles, ncolp, s);
   else if (U == 2) room = equil_sweeps<T, 2, 4>(A, m, n, ld, iters, a, part, part_doubles, ncolp, s);
   else if (U == 3) room = equil_sweeps<T, 3, 4>(A, m, n, ld, iters, a, part, part_doubles, ncolp, s);
   else if (U == 4) room = equil_sweeps<T, 4, 4>(A, m, n, ld, iters, a, part, part_doubles, ncolp, s);
