@@ -101,9 +101,21 @@ template <typename T, bool GROUPED, bool REL = false, class G> __device__ inline
 
 // argmin e^u + (r/2)(u - z)^2: e^u + r (u - z) increases in u, is positive
 // at z and negative at z - e^z / r.  Its second derivative is at most its first.
+// For z > 1 that bracket is wider than the iteration can close, but the root lies
+// between L = log(r z) and log(r (z - L)): it is 0 or more, and so L or less, where
+// L >= 0, negative and L or more where L < 0, and e^u = r (z - u) takes either
+// bound of u to the other.
 template <typename T, bool GROUPED> __device__ inline T prox_exp(T z, T r) {
   const T ez = fexp(fmin(z, T(sizeof(T) == 4 ? 80 : 700)));
-  const T lo = z - ez / r, hi = z;
+  T lo = z - ez / r, hi = z;
+  if (z > T(1)) {
+    const T lr = log(r), L = lr + log(z);
+    if (z > L) {
+      const T M = lr + log(z - L);
+      lo = fmin(L, M);
+      hi = fmin(z, fmax(L, M));
+    }
+  }
   return safe_newton<T, GROUPED>([&](T u, T &v, T &dv) {
     const T eu = fexp(u);
     v = eu + r * (u - z);
