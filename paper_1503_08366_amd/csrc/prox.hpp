@@ -130,7 +130,7 @@ template <typename T, bool GROUPED> __device__ inline T prox_exp(T z, T r) {
 template <typename T, bool GROUPED> __device__ inline T prox_neg_entr(T z, T r) {
   const T c = r * z - T(1);
   const T thi = fmin(c, log(fmax(z, T(0.36787944117144233))));
-  const T tlo = c - r * fexp(thi);
+  const T tlo = fmin(c - r * fexp(thi), thi);  // thi where c is past the type's whole numbers
   const T t = safe_newton<T, GROUPED>([&](T t, T &v, T &dv) {
     const T et = fexp(t);
     v = t + r * et - c;
