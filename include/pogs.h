@@ -108,7 +108,8 @@ typedef struct {
  * when its normal residual s = A^T (d - A x) + c - x has
  * rho ||s|| <= cg_tol * eps_dual (this iteration's dual tolerance) or after
  * cg_max_iter steps; no Gram matrix or factor is formed, so any min(m, n)
- * fits.  Each step reads A twice. */
+ * fits.  Each step reads A twice, or once for float32 A with m >= n and rows
+ * of at most 2048 entries. */
 typedef enum { POGS_PROJ_DIRECT = 0, POGS_PROJ_CGLS = 1 } pogs_projection;
 
 /* Stopping rule (Section 3.4).  RESIDUAL: stop when ||A x_h - y_h|| < eps_pri
@@ -273,10 +274,11 @@ int pogs_solve_path(pogs_ctx *ctx, int32_t R, const pogs_fn *f, const pogs_fn *g
                     const pogs_params *params, pogs_result *out);
 
 /* Residual-rule solves with the direct projection of matrices that fit the
- * registers of the GPU (rows of up to 1024 entries on the shorter side, 20 to
- * 40 MB) run a chunk of iterations in one launch whose workgroups, at most one
- * per compute unit, exchange vectors through memory and so have to be on the
- * GPU together.  Solves of one process take turns for that.  A context on a
+ * registers of the GPU (rows of up to 1024 entries on the shorter side, 20
+ * to 40 MB) run a chunk of iterations in one launch whose workgroups, at
+ * most one per compute unit, exchange vectors through memory and so have to
+ * be on the GPU together (with m < n the context keeps a transposed copy of
+ * A for them). Solves of one process take turns for that.  A context on a
  * stream restricted to some compute units runs one launch per step instead.
  * Where something else keeps the workgroups apart (long kernels on other
  * streams, another process) they give up after a bounded wait, the solve
@@ -359,8 +361,8 @@ int pogs_prox_noalloc(const pogs_fn *fn, pogs_dtype dt, double rho, const void *
  *   next one's y-side half step and column sums in the same read of A (ms[2]
  *   then covers the stop test and the finish of those column sums);
  *   CGLS (context set up for it, every projection running cg_max_iter
- *   steps): ms[1] prox step, ms[2] the two passes that start a projection,
- *   ms[3] one CG step (two passes), ms[4] = 0
+ *   steps): ms[1] prox step, ms[2] the passes that start a projection,
+ *   ms[3] one CG step, ms[4] = 0
  *   (average ms per launch sequence).
  * The solver state afterwards is meaningless; the next pogs_solve resets it.
  * Errors: EINVAL (NULL, reps < 1, no previous solve), EDEVICE. */

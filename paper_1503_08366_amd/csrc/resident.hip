@@ -44,8 +44,11 @@ bool res_all_cus(hipStream_t s) {
   return n >= res_capacity();
 }
 
-// Shapes taken: those whose rows fit the registers of the CUs (rows of up to
-// 1024 entries; 20 MB of matrix at half the CUs, 40 MB at all of them).  Of the
+// Shapes taken: those whose rows fit the registers of the CUs (20 MB of matrix at
+// half the CUs, 40 MB at all of them) and have up to 1024 entries.  The registers
+// would hold longer ones (2000 x 2000 float32 is 16 MB), but the eight waves' float64
+// column sums of a workgroup take 16 bytes an entry and wave of LDS
+// (ResShape::red_bytes), 128 of its 160 KB at 1024.  Of the
 // kernels for a row length the first that needs at most 128 workgroups, else the
 // one with the most rows: fewer, fuller workgroups cost rows per wave, more of
 // them cost exchange words (us per iteration, one launch per step / RPW and G:
